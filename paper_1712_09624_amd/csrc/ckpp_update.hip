@@ -79,14 +79,27 @@ __global__ void __launch_bounds__(256)
 // Anti-revival scan (Sec. 4.2): every bucket removes its expired entries,
 // with the counter and filter maintenance of a delete (expire_slots_pass:
 // the table is read as a stream, 16 lanes per bucket, a wavefront reading
-// four consecutive buckets, 1 KiB, per instruction).
-__global__ void __launch_bounds__(256)
+// four consecutive buckets, 1 KiB, per instruction).  The removed entries are summed in the block and added with one
+// atomic: an atomic per lane group on the one counter, which the memory side
+// performs one by one, took most of a scan that removes many.  The blocks
+// are large for the same reason.  Measured on MI355X, 2^20 buckets, 336,000
+// entries removed: 221 us with an atomic per group, 80 us with one per block
+// of 256, 53 us with one per block of 1024; nothing removed: 44 us each way
+// (6.1 TB/s); 2^24 buckets, nothing removed, 835 -> 762 us.
+constexpr uint32_t kScanBlock = 1024;
+
+__global__ void __launch_bounds__(kScanBlock)
     expire_slots_kernel(uint8_t *bk, uint64_t nb, uint32_t now, uint32_t plain_flag,
                         unsigned long long *removed) {
-  const uint64_t count =
-      expire_slots_pass(bk, nb, now, plain_flag != 0u, (uint64_t)blockIdx.x * blockDim.x + threadIdx.x,
-                        (uint64_t)gridDim.x * blockDim.x);
-  if (count && removed) atomicAdd(removed, (unsigned long long)count);
+  __shared__ unsigned long long total;
+  if (threadIdx.x == 0u) total = 0ull;
+  __syncthreads();
+  const uint64_t count = expire_slots_pass(
+      bk, nb, now, plain_flag != 0u, (uint64_t)blockIdx.x * blockDim.x + threadIdx.x,
+      (uint64_t)gridDim.x * blockDim.x);
+  if (count) atomicAdd(&total, (unsigned long long)count);
+  __syncthreads();
+  if (threadIdx.x == 0u && total && removed) atomicAdd(removed, total);
 }
 
 }  // namespace
@@ -204,10 +217,10 @@ hipError_t launch_delete(const ckpp_table *t, const void *d_keys, uint64_t n,
 hipError_t launch_expire_scan(const ckpp_table *t, uint32_t now, uint64_t *d_removed,
                               hipStream_t s) {
   const uint64_t nb = 1ull << t->log2_buckets;
-  const uint32_t block = 256;
-  // 16 lanes per bucket; a persistent grid of 16 blocks per compute unit
+  const uint32_t block = kScanBlock;
+  // 16 lanes per bucket; a persistent grid of 4 blocks per compute unit
   uint64_t grid = (16u * nb + block - 1) / block;
-  const uint64_t cap = 16ull * (uint64_t)t->num_cus;
+  const uint64_t cap = 4ull * (uint64_t)t->num_cus;
   if (grid > cap) grid = cap;
   hipLaunchKernelGGL(expire_slots_kernel, dim3((uint32_t)grid), dim3(block), 0, s, t->d_table, nb,
                      now, (t->flags & CKPP_PLAIN) ? 1u : 0u,

@@ -1038,7 +1038,7 @@ __device__ int delete_one(uint8_t *bk, uint4 key, uint32_t log2b, uint64_t seed,
 }
 
 // Anti-revival scan (Sec. 4.2) over buckets [0, nb) by the lanes gtid of a
-// grid of gthreads (blocks of 256): 16 neighbouring lanes read one bucket's
+// grid of gthreads (whole wavefronts): 16 neighbouring lanes read one bucket's
 // 256 bytes, one 16-byte quarter each, and share the metadata word (lane
 // 1), the value words (lanes 6, 7, 12, 13: the time in the high 16 bits)
 // and the other buckets (lanes 14, 15) through cross-lane reads.  Lane 0 of
