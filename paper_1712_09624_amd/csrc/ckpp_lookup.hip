@@ -159,70 +159,97 @@ __global__ void __launch_bounds__(64 * WAVES)
 
 
 template <uint32_t WAVES, uint32_t MODE, bool TIMED, uint32_t PER>
-hipError_t launch_reg(const ckpp_table *t, const TableRef &T, const uint4 *keys, uint64_t n,
-                      uint8_t *found, uint64_t *vals, hipStream_t s) {
-  const uint64_t grid =
-      capped_grid(n, 64ull * PER * WAVES, t->lookup_launch.blocks_per_cu, t->num_cus);
+hipError_t launch_reg(const ckpp_launch_t &L, int num_cus, const TableRef &T, const uint4 *keys,
+                      uint64_t n, uint8_t *found, uint64_t *vals, hipStream_t s) {
+  const uint64_t grid = capped_grid(n, 64ull * PER * WAVES, L.blocks_per_cu, num_cus);
   hipLaunchKernelGGL((lookup_reg<WAVES, MODE, TIMED, PER>), dim3((uint32_t)grid),
                      dim3(64 * WAVES), 0, s, T, keys, n, found, vals);
   return hipGetLastError();
 }
 
 template <uint32_t WAVES, uint32_t MODE, bool TIMED, uint32_t PER>
-hipError_t launch_quad(const ckpp_table *t, const TableRef &T, const uint4 *keys, uint64_t n,
-                       uint8_t *found, uint64_t *vals, hipStream_t s) {
-  const uint64_t grid =
-      capped_grid(n, 64ull * PER * WAVES, t->lookup_launch.blocks_per_cu, t->num_cus);
+hipError_t launch_quad(const ckpp_launch_t &L, int num_cus, const TableRef &T, const uint4 *keys,
+                       uint64_t n, uint8_t *found, uint64_t *vals, hipStream_t s) {
+  const uint64_t grid = capped_grid(n, 64ull * PER * WAVES, L.blocks_per_cu, num_cus);
   hipLaunchKernelGGL((lookup_quad<WAVES, MODE, TIMED, PER>), dim3((uint32_t)grid),
                      dim3(64 * WAVES), 0, s, T, keys, n, found, vals);
   return hipGetLastError();
 }
 
 template <uint32_t WAVES, uint32_t MODE, bool TIMED>
-hipError_t launch_shape(const ckpp_table *t, const TableRef &T, const uint4 *keys, uint64_t n,
-                        uint8_t *found, uint64_t *vals, hipStream_t s) {
-  const ckpp_launch_t &L = t->lookup_launch;
+hipError_t launch_shape(const ckpp_launch_t &L, int num_cus, const TableRef &T, const uint4 *keys,
+                        uint64_t n, uint8_t *found, uint64_t *vals, hipStream_t s) {
   if (L.lanes_per_lookup == 4) {
     if (L.lookups_per_lane == 2)
-      return launch_quad<WAVES, MODE, TIMED, 2>(t, T, keys, n, found, vals, s);
-    return launch_quad<WAVES, MODE, TIMED, 1>(t, T, keys, n, found, vals, s);
+      return launch_quad<WAVES, MODE, TIMED, 2>(L, num_cus, T, keys, n, found, vals, s);
+    return launch_quad<WAVES, MODE, TIMED, 1>(L, num_cus, T, keys, n, found, vals, s);
   }
   if (L.lanes_per_lookup == 1) {
     if (L.lookups_per_lane == 4)
-      return launch_reg<WAVES, MODE, TIMED, 4>(t, T, keys, n, found, vals, s);
+      return launch_reg<WAVES, MODE, TIMED, 4>(L, num_cus, T, keys, n, found, vals, s);
     if (L.lookups_per_lane == 2)
-      return launch_reg<WAVES, MODE, TIMED, 2>(t, T, keys, n, found, vals, s);
-    return launch_reg<WAVES, MODE, TIMED, 1>(t, T, keys, n, found, vals, s);
+      return launch_reg<WAVES, MODE, TIMED, 2>(L, num_cus, T, keys, n, found, vals, s);
+    return launch_reg<WAVES, MODE, TIMED, 1>(L, num_cus, T, keys, n, found, vals, s);
   }
   if (MODE != kModeBoth && L.lookups_per_lane == 2) {
     constexpr uint32_t M = MODE == kModeBoth ? kModeCuckoopp : MODE;
-    const uint64_t grid = capped_grid(n, 128ull * WAVES, L.blocks_per_cu, t->num_cus);
+    const uint64_t grid = capped_grid(n, 128ull * WAVES, L.blocks_per_cu, num_cus);
     hipLaunchKernelGGL((lookup_dual<WAVES, M, TIMED>), dim3((uint32_t)grid), dim3(64 * WAVES), 0,
                        s, T, keys, n, found, vals);
   } else {
-    const uint64_t grid = capped_grid(n, 64ull * WAVES, L.blocks_per_cu, t->num_cus);
+    const uint64_t grid = capped_grid(n, 64ull * WAVES, L.blocks_per_cu, num_cus);
     hipLaunchKernelGGL((lookup_lds<WAVES, MODE, TIMED>), dim3((uint32_t)grid), dim3(64 * WAVES),
                        0, s, T, keys, n, found, vals);
   }
   return hipGetLastError();
 }
 
-// A batch this small is bound by the latency of one lookup's few
-// dependent loads, not by requests: one lane per lookup in 64-thread blocks
-// finishes it soonest (measured on MI355X, bursts of 1..2048 lookups on a
-// 2^24-bucket table: 21.4 us p50 from submission to completion against
-// 25.4 us in the default shape).  Used while no caller set a shape.
-constexpr uint64_t kSmallBatch = 4096;
+// The shape of a batch of n lookups in mode `mode` while no caller set one.
+// The lines measured on MI355X (n lookups, times of the shape taken and of
+// {8, 2, 128}, the shape of every larger batch):
+//  - A small batch is bound by the latency of one lookup's few dependent
+//    loads, and one lane per lookup has the fewest of them between its key
+//    and its answer (65536 lookups on 2^20 buckets: 3.5 us against 7.5; 8192:
+//    2.9 against 7.4).  It stays ahead until the chip has more lookups than
+//    it can hold, since a hit reads its line twice: up to 2^18 lookups
+//    (2^20 buckets: 10.3 against 14.1 us; at 2^20 lookups 39.4 against 38.2),
+//    on tables of 4 GiB and more, whose second reads cost more, up to 2^16
+//    (2^24 buckets: 5.1 against 7.8 us; 2^17 lookups 8.1, eight lanes 6.9).
+//  - In tables that stay in the L2 caches (up to 2^15 buckets, 8 MiB; 2^16
+//    for batches up to 2^21) a second read is a hit, and 32-byte heads need
+//    a quarter of the L2's bandwidth that whole lines do: one lane per lookup
+//    at every size, two lookups per lane once that fills the chip (2^20
+//    lookups on 2^14 buckets: 18.5 against 25.4 us).
+//  - In between, eight lanes with one lookup per lane in 64-thread blocks:
+//    twice the blocks of {8, 2, 128} for a last wave of blocks half as long
+//    (2^19 lookups on 2^24 buckets 21.4 against 22.9 us).  From 2^21 lookups
+//    on both take the same time on uniform keys, and two lookups per lane are
+//    6% faster on hot ones.
+//  - The pessimistic mode, whose lookups fetch two lines at once, needs 16
+//    KiB of LDS per wavefront with eight lanes: 64-thread blocks pack more
+//    wavefronts into a compute unit, and on tables of 1 GiB and more large
+//    batches run with four lanes, which need none (2^25 lookups on 2^24
+//    buckets 1709 against 1870 us).
+ckpp_launch_t auto_shape(const ckpp_table *t, uint64_t n, uint32_t mode) {
+  const uint32_t b = t->log2_buckets;
+  const bool both = mode == kModeBoth;
+  const ckpp_launch_t one{1u, 1u, n <= (1u << 14) ? 64u : 256u, 0u};
+  if (b <= 15u) return n <= (1u << 19) ? one : ckpp_launch_t{1u, 2u, 256u, 0u};
+  const uint32_t few = b == 16u ? 21u : b < 24u ? 18u : both ? 15u : 16u;
+  if (n <= (1ull << few)) return one;
+  if (n <= (1u << 21)) return ckpp_launch_t{8u, 1u, 64u, 0u};
+  if (both) return b >= 22u ? ckpp_launch_t{4u, 1u, 128u, 0u} : ckpp_launch_t{8u, 1u, 64u, 0u};
+  return t->lookup_launch;
+}
 
 template <uint32_t MODE, bool TIMED>
 hipError_t launch_mode(const ckpp_table *t, const TableRef &T, const uint4 *keys, uint64_t n,
                        uint8_t *found, uint64_t *vals, hipStream_t s) {
-  if (!t->launch_set && n <= kSmallBatch)
-    return launch_reg<1, MODE, TIMED, 1>(t, T, keys, n, found, vals, s);
-  switch (t->lookup_launch.block) {
-    case 64: return launch_shape<1, MODE, TIMED>(t, T, keys, n, found, vals, s);
-    case 128: return launch_shape<2, MODE, TIMED>(t, T, keys, n, found, vals, s);
-    default: return launch_shape<4, MODE, TIMED>(t, T, keys, n, found, vals, s);
+  const ckpp_launch_t L = t->launch_set ? t->lookup_launch : auto_shape(t, n, MODE);
+  switch (L.block) {
+    case 64: return launch_shape<1, MODE, TIMED>(L, t->num_cus, T, keys, n, found, vals, s);
+    case 128: return launch_shape<2, MODE, TIMED>(L, t->num_cus, T, keys, n, found, vals, s);
+    default: return launch_shape<4, MODE, TIMED>(L, t->num_cus, T, keys, n, found, vals, s);
   }
 }
 
