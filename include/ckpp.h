@@ -143,14 +143,13 @@ int ckpp_clear(ckpp_table *t, void *stream);
  * d_status (n bytes, nullable) receives CKPP_INSERTED / UPDATED / FAILED /
  * RETRY; d_nfailed (one u64, nullable) is incremented by the number of
  * FAILED keys (RETRY keys are counted in ckpp_stats_t.retry_exhausted).
- * The cuckoo-path scratch of the call (4 * max_kicks bytes per launched
- * lane, at most 2^16 lanes) is a buffer of the table's own, allocated on
- * the first batch that uses it and freed with the table; it holds as many
- * lanes as a launch uses, as long as that stays within 1/32 of the table's
- * device memory (at least 4096 lanes).  A batch needing more takes its
- * scratch from the device's stream-ordered memory pool and returns it on
- * `stream`.  Two insert batches of one table must therefore not overlap in
- * time (order them on one stream).
+ * The cuckoo-path scratch of the call is a buffer of the table's own,
+ * allocated on its first insert and freed with the table: arrays of 4 *
+ * max_kicks bytes, at most 2^17 of them and at most 1/8 of the table's
+ * device memory, but at least 4096; keys that search a path beyond that many
+ * at once take turns.  (A first insert on a stream under capture takes it
+ * from the device's stream-ordered memory pool.)  Two insert batches of one table must therefore not
+ * overlap in time (order them on one stream).
  * Errors: CKPP_EINVAL (null table/keys/values with n > 0, misaligned keys),
  * CKPP_ENOMEM (scratch allocation failed). */
 int ckpp_insert_batch(ckpp_table *t, const void *d_keys, const uint64_t *d_values, uint64_t n,
@@ -161,11 +160,10 @@ int ckpp_insert_batch(ckpp_table *t, const void *d_keys, const uint64_t *d_value
  * of ckpp_insert_batch, same arguments, results and errors, that allocates
  * nothing.  Its cuckoo-path scratch is a fixed 8 MiB array in the library's
  * device memory, one per GPU, held until the process ends (instead of the
- * table's own buffer or the stream-ordered pool), so a launch uses at most
- * as many lanes as fit it: 8 MiB / (4 * max_kicks) lanes, in whole blocks
- * of 256 (4096 lanes at max_kicks 500; at least 256 for every max_kicks the
- * library accepts).  The array keeps the last call's contents; nothing in it
- * needs to start at zero (each lane writes its path before reading it).
+ * table's own buffer): at most 8 MiB / (4 * max_kicks) keys (4194 at max_kicks
+ * 500) search a path at once, and a launch has at most that many wavefronts.
+ * The array keeps the last call's contents; nothing in it needs to start at
+ * zero (each path is written before it is read).
  * Calls on one GPU share that array: two such calls that overlap in time
  * on the same GPU (on different streams, or from different threads) race
  * and corrupt each other's paths, so order them (one stream).  Not for

@@ -17,7 +17,7 @@ using ckpp::dev_status;
 
 using ckpp::kMaxLog2Buckets;
 constexpr uint32_t kMaxKicksLimit = 4096;
-constexpr uint32_t kMaxPathLanes = 65536;
+constexpr uint32_t kMaxPathLanes = 131072;
 constexpr uint32_t kAccWords = 128;   // device accumulator words
 constexpr uint32_t kAccStats = 7 + CKPP_MOVED_BINS;
 constexpr uint32_t kAccRetry = 127;   // retry-bound counter (never cleared)
@@ -203,14 +203,14 @@ int ckpp_create(ckpp_table **out, uint32_t log2_buckets, uint64_t hash_seed, uin
   if (lanes < 256) lanes = 256;
   if (lanes > kMaxPathLanes) lanes = kMaxPathLanes;
   t->path_lanes = (uint32_t)lanes;
-  // the table's own path scratch: as many lanes as a launch may use while
-  // it stays within a small share of the table's memory, at least 4096
+  // the table's own path arrays: one per lane of a launch while they stay
+  // within a small share of the table's memory, at least kOwnPathsMin
   {
-    const uint64_t lane_bytes = 4ull * (max_kicks ? max_kicks : 1u);
-    uint64_t own = table_bytes(t) / ckpp::kOwnPathShare / lane_bytes;
+    const uint64_t path_bytes = 4ull * ckpp::path_words(max_kicks);
+    uint64_t own = table_bytes(t) / ckpp::kOwnPathShare / path_bytes;
     if (own > lanes) own = lanes;
-    if (own < ckpp::kOwnPathLanesMin) own = ckpp::kOwnPathLanesMin;
-    t->own_path_lanes = (uint32_t)own;
+    if (own < ckpp::kOwnPathsMin) own = ckpp::kOwnPathsMin;
+    t->own_paths = (uint32_t)own;
   }
 
   int rc = CKPP_OK;

@@ -14,9 +14,9 @@ struct ckpp_table {
   uint64_t seed;
   uint8_t *d_table;     // 256 * 2^B bytes: bucket b at 256 * b (ckpp_device.h)
   uint32_t path_lanes;  // lanes of the persistent insert grid
-  uint32_t *d_own_paths;    // the table's own cuckoo-path scratch (own_path_lanes
-                            // lanes), allocated on the first batch that fits it
-  uint32_t own_path_lanes;
+  uint32_t *d_own_paths;    // the table's own cuckoo-path scratch (own_paths
+                            // arrays), allocated on the first insert
+  uint32_t own_paths;
   uint64_t *d_stats;    // device accumulator of ckpp_stats_t
   uint32_t retry_limit; // attempts per key on contended locks (ckpp_set_retry_limit)
   ckpp_launch_t lookup_launch;
@@ -26,15 +26,20 @@ struct ckpp_table {
 
 namespace ckpp {
 
-// Insert batches take their cuckoo-path scratch (max_kicks words per
-// launched lane) from a buffer of the table's own, kept for its lifetime,
-// when it fits: the stream-ordered pool's allocate/free pair costs tens of
-// microseconds of host time per batch, during which the device idles.  The
-// buffer holds at least kOwnPathLanesMin lanes, and more up to the launch's
-// maximum while it stays within 1/kOwnPathShare of the table's own memory;
-// larger batches use the pool.
-constexpr uint32_t kOwnPathLanesMin = 4096;
-constexpr uint64_t kOwnPathShare = 32;
+// Words of one cuckoo-path array: max_kicks entries in whole groups of four.
+inline __host__ __device__ uint32_t path_words(uint32_t max_kicks) {
+  return max_kicks ? (max_kicks + 3u) / 4u * 4u : 4u;
+}
+
+// Insert batches take their cuckoo-path scratch (arrays of path_words words,
+// shared by the lanes of a wavefront) from a buffer of the table's own, kept
+// for its lifetime: the stream-ordered pool's allocate/free pair costs tens
+// of microseconds of host time per batch, during which the device idles, and
+// hundreds where the pool has given its memory back.  The buffer holds at
+// least kOwnPathsMin arrays, and more up to one per lane of the largest
+// launch while it stays within 1/kOwnPathShare of the table's own memory.
+constexpr uint32_t kOwnPathsMin = 4096;
+constexpr uint64_t kOwnPathShare = 8;
 
 // One work item of a plan: lookups [start, start + count) of the
 // concatenated key batch, all of one table, with that table's parameters

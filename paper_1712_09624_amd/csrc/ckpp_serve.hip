@@ -597,13 +597,13 @@ template <bool TIMED>
 __device__ void insert_phase(const ServeArgs &a, uint64_t i0, uint64_t i1, uint32_t now) {
   const uint64_t g = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
   if (g >= a.path_lanes) return;
-  uint32_t *path = a.paths + g * (uint64_t)(a.max_kicks ? a.max_kicks : 1u);
+  uint32_t *path = a.paths + g * (uint64_t)path_words(a.max_kicks);
   const uint32_t expiry = (now + a.ttl) & 0xffffu;
   for (uint64_t j = i0 + column_rank(g, a.path_lanes, false); j < i1; j += a.path_lanes) {
     const uint64_t slot = j & a.mask;
     const InsertOutcome o =
         insert_one<TIMED>(a.bk, a.in_keys[slot], a.in_vals[slot], a.T.log2b, a.T.seed,
-                          a.max_kicks, a.plain != 0u, path, a.spin_limit, expiry, now);
+                          a.max_kicks, a.plain != 0u, LanePath{path}, a.spin_limit, expiry, now);
     put_result(a.in_status + slot, (uint8_t)o.status);
     if (o.spun) atomicAdd(a.nspin, 1ull);
   }
@@ -997,7 +997,7 @@ int ckpp_server_create(ckpp_server **out, ckpp_table *t, const ckpp_server_confi
   const uint32_t bpc = std::min<uint32_t>(c.blocks_per_cu, (uint32_t)std::max(per_cu, 1));
   s->grid = bpc * (uint32_t)t->num_cus;
   const uint32_t path_lanes = std::min<uint32_t>(ckpp::kMaxPathLanes, s->grid * ckpp::kBlock);
-  const uint64_t path_words = (uint64_t)path_lanes * (t->max_kicks ? t->max_kicks : 1u);
+  const uint64_t path_words = (uint64_t)path_lanes * ckpp::path_words(t->max_kicks);
   if (e == hipSuccess) e = hipMalloc(&s->paths, path_words * 4);
   if (e == hipSuccess) e = hipMalloc(&s->dev, sizeof(ServeDev));
   if (e == hipSuccess) e = hipMemset(s->dev, 0, sizeof(ServeDev));

@@ -14,6 +14,8 @@ namespace {
 // its name as an address: the device address comes from
 // hipGetSymbolAddress, once per device (scratch_on).
 constexpr uint64_t kScratchBytes = 8ull << 20;
+static __device__ __align__(256) uint32_t scratch[kScratchBytes / sizeof(uint32_t)];
+
 // Batches of at most this many keys run one key per wavefront (its lane 0):
 // a wavefront runs its lanes' updates in lockstep, so a few keys side by
 // side in one wavefront take several times as long as one key alone
@@ -35,28 +37,124 @@ __device__ __forceinline__ bool worker_of(bool spread, uint64_t &worker, uint64_
   nworkers = nlanes >> 6;
   return (threadIdx.x & 63u) == 0u;
 }
-static __device__ __align__(256) uint32_t scratch[kScratchBytes / sizeof(uint32_t)];
 
-// TIMED: the table has timers; expiry[i] is key i's expiration time and
-// `now` the current time (Sec. 4.2).
+// What an insert launch needs.  TIMED kernels: expiry[i] is key i's
+// expiration time and `now` the current time (Sec. 4.2).
+struct InsertArgs {
+  uint8_t *bk;
+  const uint4 *keys;
+  const uint64_t *vals;
+  const uint16_t *expiry;
+  uint64_t n;
+  uint64_t seed;
+  uint32_t now, log2b, max_kicks, plain, spin_limit;
+  uint32_t *paths;       // every wavefront's path arrays, wave_paths each
+  uint32_t wave_paths;   // 1..64
+  uint8_t *status;       // nullable
+  unsigned long long *nfailed, *nspin;  // nullable
+};
+
+// Adds the number of the wavefront's lanes for which `p` holds to *ctr.
+__device__ __forceinline__ void count_lanes(bool p, unsigned long long *ctr) {
+  const uint64_t m = __builtin_amdgcn_ballot_w64(p);
+  if (m != 0ull && ctr && (threadIdx.x & 63u) == (uint32_t)__builtin_ctzll(m))
+    atomicAdd(ctr, (unsigned long long)__builtin_popcountll(m));
+}
+
+// Key i through the whole state machine; every lane of the wavefront calls
+// this together, `ok` for those that have a key.
 template <bool TIMED>
-__global__ void __launch_bounds__(256)
-    insert_kernel(uint8_t *bk, const uint4 *__restrict__ keys,
-                  const uint64_t *__restrict__ vals, const uint16_t *__restrict__ expiry,
-                  uint32_t now, uint64_t n, uint32_t log2b, uint64_t seed,
-                  uint32_t max_kicks, uint32_t plain_flag, uint32_t spin_limit, uint32_t *paths,
-                  uint8_t *__restrict__ status, unsigned long long *nfailed,
-                  unsigned long long *nspin, uint32_t spread) {
-  const bool plain = plain_flag != 0u;
+__device__ __forceinline__ void insert_key(const InsertArgs &A, uint64_t i, bool ok,
+                                           const WavePath &paths) {
+  InsertOutcome o{CKPP_INSERTED, false};
+  if (ok) {
+    o = insert_one<TIMED>(A.bk, A.keys[i], A.vals[i], A.log2b, A.seed, A.max_kicks, A.plain != 0u,
+                          paths, A.spin_limit, TIMED ? A.expiry[i] : 0u, A.now);
+    if (A.status) A.status[i] = (uint8_t)o.status;
+  }
+  count_lanes(o.status == CKPP_FAILED, A.nfailed);
+  count_lanes(o.spun, A.nspin);
+}
+
+__device__ __forceinline__ WavePath wave_paths(const InsertArgs &A, unsigned long long *held) {
+  const uint64_t wave = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  return WavePath{A.paths + wave * A.wave_paths * path_words(A.max_kicks), A.wave_paths,
+                  held + (threadIdx.x >> 6)};
+}
+
+// One key per wavefront (its lane 0).
+template <bool TIMED>
+__global__ void __launch_bounds__(256) insert_spread(InsertArgs A) {
+  __shared__ unsigned long long s_held[4];
+  if (threadIdx.x < 4u) s_held[threadIdx.x] = 0ull;
+  __syncthreads();
   uint64_t worker, nworkers;
-  if (!worker_of(spread != 0u, worker, nworkers)) return;
-  uint32_t *path = paths + worker * (uint64_t)(max_kicks ? max_kicks : 1u);
-  for (uint64_t i = worker; i < n; i += nworkers) {
-    const InsertOutcome o = insert_one<TIMED>(bk, keys[i], vals[i], log2b, seed, max_kicks, plain,
-                                              path, spin_limit, TIMED ? expiry[i] : 0u, now);
-    if (status) status[i] = (uint8_t)o.status;
-    if (o.status == CKPP_FAILED && nfailed) atomicAdd(nfailed, 1ull);
-    if (o.spun && nspin) atomicAdd(nspin, 1ull);
+  const bool first = worker_of(true, worker, nworkers);
+  const WavePath paths = wave_paths(A, s_held);
+  for (uint64_t i = worker; i < A.n; i += nworkers) insert_key<TIMED>(A, i, first, paths);
+}
+
+// One lane per key, 64 keys per wavefront at a time, in two stages.  The
+// first does what the primary's lock alone decides (insert_primary): a few
+// round trips, the same for every lane.  A key that needs more (its
+// secondary, a cuckoo path, another try at a held lock) goes into the
+// wavefront's list, and once 64 are waiting the wavefront runs their state
+// machines together.  A wavefront runs its lanes in lockstep, so slow keys
+// run one by one as they come would each hold up 63 lanes that are done.
+// A batch of one key per lane has nothing to gather and runs the state
+// machines at once.  Measured on MI355X, 32M slots built to load 0.95 in one
+// call: 9.5 ms without the list, 8.8 ms with it, 7.7 ms with it on 2^17 lanes
+// (two wavefronts per SIMD) instead of 2^16; 2^18 lanes: 8.0 ms.
+template <bool TIMED>
+__global__ void __launch_bounds__(256) insert_lanes(InsertArgs A) {
+  __shared__ unsigned long long s_held[4];
+  __shared__ uint64_t s_wait[4][128];
+  if (threadIdx.x < 4u) s_held[threadIdx.x] = 0ull;
+  __syncthreads();
+  const uint32_t lane = threadIdx.x & 63u;
+  const WavePath paths = wave_paths(A, s_held);
+  uint64_t *wait = s_wait[threadIdx.x >> 6];
+  uint32_t waiting = 0u;
+  const bool plain = A.plain != 0u;
+  const uint64_t wave = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+  if (A.n <= stride) {
+    const uint64_t i = wave * 64u + lane;
+    insert_key<TIMED>(A, i, i < A.n, paths);
+    return;
+  }
+  for (uint64_t i0 = wave * 64u; i0 < A.n; i0 += stride) {
+    const uint64_t i = i0 + lane;
+    bool later = i < A.n;
+    if (later && !plain) {
+      const uint4 key = A.keys[i];
+      const uint64_t value = A.vals[i];
+      const bool wide = TIMED && (value >> kTimerShift) != 0ull;  // fails: not here
+      const uint64_t word = TIMED ? value | ((uint64_t)A.expiry[i] << kTimerShift) : value;
+      const KeyFields f = key_fields(key_hash(key, A.seed), A.log2b);
+      if (!wide && try_lock(A.bk, f.p)) {
+        section_begin();
+        const int r = insert_primary<TIMED>(A.bk, key, word, f, read_head(A.bk, f.p), false, A.now);
+        if (r == kNeedPair) {
+          unlock(A.bk, f.p);
+        } else {
+          if (A.status) A.status[i] = (uint8_t)r;
+          later = false;
+        }
+      }
+    }
+    const uint64_t m = __builtin_amdgcn_ballot_w64(later);
+    if (later) wait[waiting + (uint32_t)__builtin_popcountll(m & ((1ull << lane) - 1ull))] = i;
+    waiting += (uint32_t)__builtin_popcountll(m);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (waiting >= 64u) {
+      waiting -= 64u;
+      insert_key<TIMED>(A, wait[waiting + lane], true, paths);
+    }
+  }
+  if (waiting) {
+    const bool ok = lane < waiting;
+    insert_key<TIMED>(A, ok ? wait[lane] : 0ull, ok, paths);
   }
 }
 
@@ -104,46 +202,81 @@ __global__ void __launch_bounds__(kScanBlock)
 
 }  // namespace
 
+namespace {
+
+// Launches an insert of A.n keys with `npaths` path arrays at A.paths
+// (npaths >= kMinPaths): one key per wavefront for few keys, else one lane
+// per key on at most t->path_lanes lanes and npaths wavefronts.
+hipError_t launch_insert_kernel(const ckpp_table *t, InsertArgs A, bool timed, uint64_t npaths,
+                                hipStream_t s) {
+  const bool spread = A.n <= kSpreadKeys && A.n <= npaths;
+  const uint32_t block = 256, waves = block / 64u;
+  uint64_t lanes = spread ? 64u * A.n : A.n < t->path_lanes ? A.n : t->path_lanes;
+  if (lanes > 64u * npaths) lanes = 64u * npaths;
+  uint64_t grid = (lanes + block - 1) / block;
+  if (grid * waves > npaths) grid = npaths / waves;
+  const uint64_t per_wave = npaths / (grid * waves);
+  A.wave_paths = per_wave < 64u ? (uint32_t)per_wave : 64u;
+  const dim3 g((uint32_t)grid), b(block);
+  if (timed) {
+    if (spread) hipLaunchKernelGGL(insert_spread<true>, g, b, 0, s, A);
+    else hipLaunchKernelGGL(insert_lanes<true>, g, b, 0, s, A);
+  } else {
+    if (spread) hipLaunchKernelGGL(insert_spread<false>, g, b, 0, s, A);
+    else hipLaunchKernelGGL(insert_lanes<false>, g, b, 0, s, A);
+  }
+  return hipGetLastError();
+}
+
+InsertArgs insert_args(const ckpp_table *t, const void *d_keys, const uint64_t *d_values,
+                       const uint16_t *d_expiry, uint32_t now, uint64_t n, uint32_t *paths,
+                       uint8_t *d_status, uint64_t *d_nfailed) {
+  InsertArgs A;
+  A.bk = t->d_table;
+  A.keys = reinterpret_cast<const uint4 *>(d_keys);
+  A.vals = d_values;
+  A.expiry = d_expiry;
+  A.n = n;
+  A.seed = t->seed;
+  A.now = now;
+  A.log2b = t->log2_buckets;
+  A.max_kicks = t->max_kicks;
+  A.plain = (t->flags & CKPP_PLAIN) ? 1u : 0u;
+  A.spin_limit = t->retry_limit;
+  A.paths = paths;
+  A.wave_paths = 1u;
+  A.status = d_status;
+  A.nfailed = reinterpret_cast<unsigned long long *>(d_nfailed);
+  A.nspin = reinterpret_cast<unsigned long long *>(t->d_stats) + 127;
+  return A;
+}
+
+}  // namespace
+
 hipError_t launch_insert(const ckpp_table *t, const void *d_keys, const uint64_t *d_values,
                          const uint16_t *d_expiry, const TimerArgs *timers, uint64_t n,
                          uint8_t *d_status, uint64_t *d_nfailed, hipStream_t s) {
-  const bool spread = n <= kSpreadKeys;
-  const uint64_t lanes = spread ? 64u * n : n < t->path_lanes ? n : t->path_lanes;
-  const uint32_t block = 256;
-  const uint32_t grid = (uint32_t)((lanes + block - 1) / block);
-  // cuckoo-path scratch of this batch, one path of max_kicks entries per
-  // key slot (a lane, or a wavefront when spread): the table's own buffer
-  // when it is large enough, else stream-ordered from the device's pool
-  const uint64_t per_lane = (uint64_t)(t->max_kicks ? t->max_kicks : 1u);
-  const uint64_t slots = (uint64_t)grid * (spread ? block / 64u : block);
-  const uint64_t words = slots * per_lane;
-  uint32_t *paths = nullptr;
-  const bool own = slots <= t->own_path_lanes;
+  ckpp_table *tm = const_cast<ckpp_table *>(t);
+  const uint64_t bytes = (uint64_t)t->own_paths * path_words(t->max_kicks) * sizeof(uint32_t);
+  uint32_t *paths = t->d_own_paths;
   hipError_t e = hipSuccess;
-  if (own) {
-    ckpp_table *tm = const_cast<ckpp_table *>(t);
-    if (!tm->d_own_paths)
-      e = hipMalloc(reinterpret_cast<void **>(&tm->d_own_paths),
-                    (uint64_t)t->own_path_lanes * per_lane * sizeof(uint32_t));
-    paths = tm->d_own_paths;
-  } else {
-    e = hipMallocAsync(reinterpret_cast<void **>(&paths), words * sizeof(uint32_t), s);
+  bool pooled = false;
+  if (!paths) {
+    // a stream under capture cannot allocate the table's buffer: that one
+    // batch takes its scratch from the stream-ordered pool
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    e = hipStreamIsCapturing(s, &capture);
+    if (e != hipSuccess) return e;
+    pooled = capture != hipStreamCaptureStatusNone;
+    e = pooled ? hipMallocAsync(reinterpret_cast<void **>(&paths), bytes, s)
+               : hipMalloc(reinterpret_cast<void **>(&paths), bytes);
+    if (e != hipSuccess) return e;
+    if (!pooled) tm->d_own_paths = paths;
   }
-  if (e != hipSuccess) return e;
-  unsigned long long *nspin = reinterpret_cast<unsigned long long *>(t->d_stats) + 127;
-  const uint32_t plain = (t->flags & CKPP_PLAIN) ? 1u : 0u;
-  unsigned long long *nfailed = reinterpret_cast<unsigned long long *>(d_nfailed);
-  const uint4 *keys = reinterpret_cast<const uint4 *>(d_keys);
-  if (timers)
-    hipLaunchKernelGGL(insert_kernel<true>, dim3(grid), dim3(block), 0, s, t->d_table, keys,
-                       d_values, d_expiry, timers->now, n, t->log2_buckets, t->seed, t->max_kicks,
-                       plain, t->retry_limit, paths, d_status, nfailed, nspin, spread ? 1u : 0u);
-  else
-    hipLaunchKernelGGL(insert_kernel<false>, dim3(grid), dim3(block), 0, s, t->d_table, keys,
-                       d_values, nullptr, 0u, n, t->log2_buckets, t->seed, t->max_kicks, plain,
-                       t->retry_limit, paths, d_status, nfailed, nspin, spread ? 1u : 0u);
-  e = hipGetLastError();
-  if (own) return e;
+  const InsertArgs A = insert_args(t, d_keys, d_values, d_expiry, timers ? timers->now : 0u, n,
+                                   paths, d_status, d_nfailed);
+  e = launch_insert_kernel(t, A, timers != nullptr, t->own_paths, s);
+  if (!pooled) return e;
   const hipError_t f = hipFreeAsync(paths, s);
   return e != hipSuccess ? e : f;
 }
@@ -172,26 +305,16 @@ uint32_t *scratch_on(int dev) {
 
 }  // namespace
 
-// The insert of launch_insert with its path scratch in `scratch`: at most
-// as many lanes as fit kScratchBytes (whole blocks of 256), no allocation.
+// The insert of launch_insert with its path arrays in `scratch`, no
+// allocation.
 int insert_noalloc(const ckpp_table *t, const void *d_keys, const uint64_t *d_values, uint64_t n,
                    uint8_t *d_status, uint64_t *d_nfailed, hipStream_t s) {
-  const uint64_t per_lane = (uint64_t)(t->max_kicks ? t->max_kicks : 1u);
-  const uint32_t block = 256;
-  const uint64_t fit = kScratchBytes / (per_lane * sizeof(uint32_t)) / block * block;
-  if (fit == 0) return CKPP_EINVAL;  // a path longer than the whole array
+  const uint64_t path_bytes = path_words(t->max_kicks) * sizeof(uint32_t);
   uint32_t *paths = scratch_on(t->device);
   if (!paths) return CKPP_EDEVICE;
-  uint64_t lanes = n < t->path_lanes ? n : t->path_lanes;
-  if (lanes > fit) lanes = fit;
-  const uint32_t grid = (uint32_t)((lanes + block - 1) / block);
-  unsigned long long *nspin = reinterpret_cast<unsigned long long *>(t->d_stats) + 127;
-  const uint32_t plain = (t->flags & CKPP_PLAIN) ? 1u : 0u;
-  hipLaunchKernelGGL(insert_kernel<false>, dim3(grid), dim3(block), 0, s, t->d_table,
-                     reinterpret_cast<const uint4 *>(d_keys), d_values, nullptr, 0u, n,
-                     t->log2_buckets, t->seed, t->max_kicks, plain, t->retry_limit, paths,
-                     d_status, reinterpret_cast<unsigned long long *>(d_nfailed), nspin, 0u);
-  return dev_status(hipGetLastError());
+  const InsertArgs A =
+      insert_args(t, d_keys, d_values, nullptr, 0u, n, paths, d_status, d_nfailed);
+  return dev_status(launch_insert_kernel(t, A, false, kScratchBytes / path_bytes, s));
 }
 
 hipError_t launch_delete(const ckpp_table *t, const void *d_keys, uint64_t n,

@@ -250,6 +250,11 @@ __device__ __forceinline__ void write_entry(uint8_t *bk, uint32_t b, uint32_t s,
   other_ptr(bk, b)[s] = other;
 }
 
+// A random number below n (n <= 8) from the 64 random bits r.
+__device__ __forceinline__ uint32_t random_below(uint64_t r, uint32_t n) {
+  return __umulhi((uint32_t)(r >> 32), n);
+}
+
 // Index of the k-th set bit of m (k < popcount(m)).
 __device__ __forceinline__ uint32_t nth_bit(uint32_t m, uint32_t k) {
   for (uint32_t i = 0; i < k; ++i) m &= m - 1u;
@@ -272,6 +277,7 @@ constexpr int kBusy = -2;    // a lock was taken by another lane: retry
 constexpr int kDisplaceBusy = -3;
 constexpr uint32_t kDisplaceRetries = 4;
 constexpr int kNeedPath = -1;
+constexpr int kNeedPair = -4;  // p's lock alone does not decide the key
 
 // Busy slots of bucket b whose entries have expired at `now`.
 __device__ __forceinline__ uint32_t expired_mask(uint8_t *bk, uint32_t b, uint32_t busy,
@@ -439,8 +445,8 @@ __device__ __attribute__((noinline)) int displace_and_place(uint8_t *bk, uint32_
   uint32_t v = kSlots, y1 = kNoBucket, t = kSlots, y2 = kNoBucket;
   if (room) {
     const uint32_t pick = (room & sec) ? (room & sec) : room;
-    v = nth_bit(pick, (uint32_t)(mix64(h ^ kDisplaceSalt) %
-                                 (uint64_t)__builtin_popcount(pick)));
+    v = nth_bit(pick, random_below(mix64(h ^ kDisplaceSalt),
+                                   (uint32_t)__builtin_popcount(pick)));
     y1 = pick_slot(other, v);
   } else {
     // second level, one candidate at a time in the order of the choice
@@ -556,6 +562,44 @@ __device__ __forceinline__ bool lock_second(uint8_t *bk, const KeyFields &f, boo
   return false;
 }
 
+// The key's entry, in slot s of bucket b (locked), gets a new value: an
+// update, or with timers an expired one overwritten in place.
+template <bool TIMED>
+__device__ __forceinline__ int update_entry(uint8_t *bk, uint32_t b, uint32_t s, uint64_t word,
+                                            uint32_t now) {
+  const Coh<uint64_t> vw = value_ptr(bk, b, s)[0];
+  const int r = !TIMED || word_alive(vw, now) ? CKPP_UPDATED : CKPP_INSERTED;
+  vw = word;
+  return r;
+}
+
+// What p's lock alone decides (see insert_direct): hp is p's head, read
+// under its lock.  Updates the key in p, or places one that is in neither
+// bucket there, and drops p's lock; or returns kNeedPair, having changed
+// nothing, with p still locked.
+template <bool TIMED>
+__device__ __forceinline__ int insert_primary(uint8_t *bk, uint4 key, uint64_t word,
+                                              const KeyFields &f, const Head &hp, bool plain,
+                                              uint32_t now) {
+  const int s = find_slot(bk, f.p, hp, key, f.tag);
+  if (s >= 0) {
+    const int r = update_entry<TIMED>(bk, f.p, (uint32_t)s, word, now);
+    section_end();
+    unlock(bk, f.p);
+    return r;
+  }
+  if (plain || bloom_pass(hp.q1, f.bloom_bits)) return kNeedPair;
+  const uint32_t meta = hp.q1.z, busy = meta_busy(meta);
+  uint32_t room = ~busy & 0xffu;
+  if (TIMED && !room) room = expired_mask(bk, f.p, busy, now) & ~meta_sec(meta);
+  if (!room) return kNeedPair;
+  const uint32_t fs = (uint32_t)__builtin_ctz(room), bit = 1u << fs;
+  write_entry(bk, f.p, fs, key, word, f.tag, f.a);
+  section_end();
+  unlock_meta(bk, f.p, make_meta(meta_moved(meta), busy | bit, meta_sec(meta) & ~bit));
+  return CKPP_INSERTED;
+}
+
 // The DIRECT step of an absent key under the locks of both its buckets: the
 // lowest free slot of p, else of a; with timers also a slot whose entry has
 // expired, after the free ones of its bucket; else displacements.  Drops
@@ -643,46 +687,68 @@ __device__ int insert_direct(uint8_t *bk, uint4 key, uint64_t word, const KeyFie
                              uint64_t h, uint32_t log2b, uint64_t seed, bool plain, uint32_t now,
                              bool retry_displace, bool &pair) {
   if (!lock_start(bk, f, pair)) return kBusy;
-  bool both = pair;  // a's lock is held too
+  const bool both = pair;  // a's lock is held too
   const Head hp = read_head(bk, f.p);
-  Pair P{{f.p, f.a}, {hp.q1.z, 0u}, (uint64_t)hp.q1.x | ((uint64_t)hp.q1.y << 32)};
-  int s = find_slot(bk, f.p, hp, key, f.tag);
-  uint32_t b = f.p;
-  const bool pass = plain || bloom_pass(hp.q1, f.bloom_bits);
-  if (s < 0 && !pass) {
-    const uint32_t busy = meta_busy(P.meta[0]);
-    uint32_t room = ~busy & 0xffu;
-    if (TIMED && !room) room = expired_mask(bk, f.p, busy, now) & ~meta_sec(P.meta[0]);
-    if (room) {
-      const uint32_t fs = (uint32_t)__builtin_ctz(room), bit = 1u << fs;
-      write_entry(bk, f.p, fs, key, word, f.tag, f.a);
-      section_end();
-      unlock_meta(bk, f.p, make_meta(meta_moved(P.meta[0]), busy | bit, meta_sec(P.meta[0]) & ~bit));
-      if (both) unlock(bk, f.a);
-      return CKPP_INSERTED;
+  const int r = insert_primary<TIMED>(bk, key, word, f, hp, plain, now);
+  if (r != kNeedPair) {
+    if (both) unlock(bk, f.a);
+    return r;
+  }
+  if (!lock_second(bk, f, pair)) return kBusy;
+  const Head ha = read_head(bk, f.a);
+  if (plain || bloom_pass(hp.q1, f.bloom_bits)) {
+    const int s = find_slot(bk, f.a, ha, key, f.tag);
+    if (s >= 0) {
+      const int u = update_entry<TIMED>(bk, f.a, (uint32_t)s, word, now);
+      unlock_two(bk, f.p, f.a);
+      return u;
     }
   }
-  if (s < 0) {
-    if (!lock_second(bk, f, pair)) return kBusy;
-    const Head ha = read_head(bk, f.a);
-    P.meta[1] = ha.q1.z;
-    if (pass) {
-      s = find_slot(bk, f.a, ha, key, f.tag);
-      b = f.a;
-    }
-    if (s < 0) return insert_pair<TIMED>(bk, key, word, f, h, log2b, seed, plain, now,
-                                         retry_displace, P);
-    both = true;
+  Pair P{{f.p, f.a}, {hp.q1.z, ha.q1.z}, (uint64_t)hp.q1.x | ((uint64_t)hp.q1.y << 32)};
+  return insert_pair<TIMED>(bk, key, word, f, h, log2b, seed, plain, now, retry_displace, P);
+}
+
+// A cuckoo path's entries in memory (bucket | slot << 29), in groups of
+// four, group g at p + g * step words (16-byte aligned): a wavefront's path
+// arrays are interleaved group by group, so that the lanes of a walk, which
+// advance together, read neighbouring groups.  An array holds path_words
+// words.
+struct PathRef {
+  uint32_t *p;
+  uint32_t step;
+  __device__ __forceinline__ uint32_t &operator[](uint32_t i) const {
+    return p[(uint64_t)(i >> 2) * step + (i & 3u)];
   }
-  // the key's entry: an update, or with timers an expired one overwritten in
-  // place
-  const Coh<uint64_t> vw = value_ptr(bk, b, (uint32_t)s)[0];
-  const int r = !TIMED || word_alive(vw, now) ? CKPP_UPDATED : CKPP_INSERTED;
-  vw = word;
-  section_end();
-  unlock(bk, f.p);
-  if (both) unlock(bk, f.a);
-  return r;
+  __device__ __forceinline__ uint4 group(uint32_t g) const {
+    return *reinterpret_cast<const uint4 *>(p + (uint64_t)g * step);
+  }
+};
+
+// Slots of bucket b among the first n entries of the path.  A walk that
+// finds no way out looks through its whole path at every step, which takes
+// most of its time: the entries are loaded kScan groups at a time (a key
+// that fails after 500 steps: 12.0 ms entry by entry, @@ ms this way).
+constexpr uint32_t kScan = 12;
+
+__device__ __forceinline__ uint32_t path_slots(PathRef path, uint32_t n, uint32_t b) {
+  uint32_t used = 0u;
+  for (uint32_t i = 0; i < n; i += 4u * kScan) {
+    uint4 e[kScan];
+#pragma unroll
+    for (uint32_t g = 0; g < kScan; ++g) {
+      const uint32_t at = i + 4u * g;
+      e[g] = path.group((at < n ? at : i) >> 2);
+    }
+#pragma unroll
+    for (uint32_t g = 0; g < kScan; ++g) {
+      const uint32_t w[4] = {e[g].x, e[g].y, e[g].z, e[g].w};
+#pragma unroll
+      for (uint32_t k = 0; k < 4u; ++k)
+        if (i + 4u * g + k < n && (w[k] & kPathBucketMask) == b)
+          used |= 1u << (w[k] >> kPathSlotShift);
+    }
+  }
+  return used;
 }
 
 // Random walk with one step of lookahead from bucket `start` (read without
@@ -699,7 +765,7 @@ __device__ int insert_direct(uint8_t *bk, uint4 key, uint64_t word, const KeyFie
 // bucket with a free slot that ends the path.  Returns the path length, or
 // -1.
 __device__ __attribute__((noinline)) int walk(const uint8_t *bk, uint32_t start, uint64_t rbase, uint32_t max_kicks,
-                    bool plain, uint32_t *path, uint32_t *last) {
+                    bool plain, PathRef path, uint32_t *last) {
   uint32_t cur = start, prev = kNoBucket;
   for (uint32_t step = 0; step < max_kicks; ++step) {
     const uint8_t *base = bucket_ptr(bk, cur);
@@ -711,11 +777,7 @@ __device__ __attribute__((noinline)) int walk(const uint8_t *bk, uint32_t start,
       other[2 * w] = (uint32_t)o;
       other[2 * w + 1] = (uint32_t)(o >> 32);
     }
-    uint32_t used = 0;
-    for (uint32_t i = 0; i < step; ++i) {
-      const uint32_t e = path[i];
-      if ((e & kPathBucketMask) == cur) used |= 1u << (e >> kPathSlotShift);
-    }
+    const uint32_t used = path_slots(path, step, cur);
     const uint32_t sec = meta_sec(meta);
     uint32_t cand = meta_busy(meta) & ~used;
     if (!plain && meta_moved(meta) >= 0xffffu) cand &= sec;  // no owner may leave
@@ -735,7 +797,7 @@ __device__ __attribute__((noinline)) int walk(const uint8_t *bk, uint32_t start,
     const uint64_t r = mix64(rbase + (uint64_t)(step + 1) * kGolden);
     if (room) {
       const uint32_t pick = (room & sec) ? (room & sec) : room;
-      const uint32_t v = nth_bit(pick, (uint32_t)(r % (uint64_t)__builtin_popcount(pick)));
+      const uint32_t v = nth_bit(pick, random_below(r, (uint32_t)__builtin_popcount(pick)));
       path[step] = cur | (v << kPathSlotShift);
       *last = pick_slot(other, v);
       return (int)step + 1;
@@ -746,7 +808,7 @@ __device__ __attribute__((noinline)) int walk(const uint8_t *bk, uint32_t start,
       if (((cand >> s) & 1u) && other[s] != prev) pref |= 1u << s;
     const uint32_t home = pref & sec;
     const uint32_t pick = home ? home : (pref ? pref : cand);
-    const uint32_t v = nth_bit(pick, (uint32_t)(r % (uint64_t)__builtin_popcount(pick)));
+    const uint32_t v = nth_bit(pick, random_below(r, (uint32_t)__builtin_popcount(pick)));
     path[step] = cur | (v << kPathSlotShift);
     prev = cur;
     cur = pick_slot(other, v);
@@ -829,7 +891,7 @@ constexpr uint32_t kSectionPath = 8;
 // read 0 only when the earlier one found the lock held by another lane that
 // has let it go since, and then this lane holds it through the repeat and
 // gives it back with the others.
-__device__ __attribute__((noinline)) int apply_path(uint8_t *bk, const uint32_t *path,
+__device__ __attribute__((noinline)) int apply_path(uint8_t *bk, PathRef path,
                                                     uint32_t len, uint32_t last, uint32_t log2b,
                                                     uint64_t seed, bool plain) {
   uint32_t b[kSectionPath + 1], sl[kSectionPath];
@@ -892,6 +954,40 @@ __device__ __attribute__((noinline)) int apply_path(uint8_t *bk, const uint32_t 
   return r;
 }
 
+// Where a key's walk writes its path: a fixed array of the lane's own.
+struct LanePath {
+  uint32_t *p;
+  __device__ __forceinline__ bool take(PathRef &path) const {
+    path = PathRef{p, 4u};
+    return true;
+  }
+  __device__ __forceinline__ void give() const {}
+};
+
+// One of the `count` path arrays (1..64, interleaved from `base`) of a
+// wavefront.  Few keys walk, so a wavefront's lanes share fewer arrays than
+// it has lanes: lane l may take array l mod count, when no other lane holds
+// it (its bit in `held`, a word of LDS), and keeps it until its key is done.
+// A lane that finds its array held tries again in its next iteration; the
+// holder, a lane of the same wavefront, goes on meanwhile.
+struct WavePath {
+  uint32_t *base;
+  uint32_t count;
+  unsigned long long *held;
+  bool mine = false;
+  __device__ __forceinline__ uint32_t slot() const { return (threadIdx.x & 63u) % count; }
+  __device__ __forceinline__ bool take(PathRef &path) {
+    const uint32_t i = slot();
+    if (!mine) mine = ((atomicOr(held, 1ull << i) >> i) & 1ull) == 0ull;
+    path = PathRef{base + 4u * i, 4u * count};
+    return mine;
+  }
+  __device__ __forceinline__ void give() {
+    if (mine) atomicAnd(held, ~(1ull << slot()));
+    mine = false;
+  }
+};
+
 // Outcome of one key's insert: its status, and whether the retry bound ran
 // out (then the status is CKPP_RETRY).
 struct InsertOutcome {
@@ -902,14 +998,15 @@ struct InsertOutcome {
 // Runs one key through the DIRECT / WALK / MOVE state machine until it is
 // placed, updated or fails, for at most spin_limit iterations (then
 // CKPP_RETRY: the key's value is neither stored nor changed; the moves
-// applied so far only relocated other entries).  path: this lane's scratch,
-// max(1, max_kicks) words.  TIMED: the table has timers; the entry gets
+// applied so far only relocated other entries).  paths: where the path
+// scratch (path_words words) comes from; an iteration that only waits
+// for it is not counted.  TIMED: the table has timers; the entry gets
 // expiration time `expiry`, and a value of 2^48 or more (the device layout's
 // limit) fails at once with nothing changed.
-template <bool TIMED = false>
+template <bool TIMED = false, class Paths>
 __device__ InsertOutcome insert_one(uint8_t *bk, uint4 key, uint64_t value, uint32_t log2b,
                                     uint64_t seed, uint32_t max_kicks, bool plain,
-                                    uint32_t *path, uint32_t spin_limit, uint32_t expiry = 0u,
+                                    Paths paths, uint32_t spin_limit, uint32_t expiry = 0u,
                                     uint32_t now = 0u) {
   if (TIMED && (value >> kTimerShift) != 0ull) return InsertOutcome{CKPP_FAILED, false};
   const uint64_t word = TIMED ? (value | ((uint64_t)(expiry & 0xffffu) << kTimerShift)) : value;
@@ -919,55 +1016,69 @@ __device__ InsertOutcome insert_one(uint8_t *bk, uint4 key, uint64_t value, uint
   int state = DIRECT, result = -1;
   uint32_t len = 0, next = 0, last = 0, walks = 0, iters = 0, dretries = 0;
   bool spun = false;
+  PathRef path{nullptr, 0u};
   // a table without filters needs both buckets for every key
   bool pair = plain;
-  while (result < 0) {
-    if (++iters > spin_limit) {
-      result = CKPP_RETRY;
-      spun = true;
-      break;
-    }
-    if (state == DIRECT) {
-      const bool retry_displace = dretries < kDisplaceRetries;
-      const int r = insert_direct<TIMED>(bk, key, word, f, h, log2b, seed, plain, now,
-                                         retry_displace, pair);
-      if (r >= 0)
-        result = r;
-      else if (r == kNeedPath)
-        state = WALK;
-      else if (r == kDisplaceBusy)
-        ++dretries;  // DIRECT again
-    } else if (state == WALK) {
-      if (walks >= kMaxWalks) {
-        result = CKPP_FAILED;
-        break;
-      }
-      const int L = walk(bk, f.p, h ^ ((uint64_t)walks * kWalkSalt), max_kicks, plain,
-                         path, &last);
-      ++walks;
-      if (L <= 0) {
-        result = CKPP_FAILED;
+  uint32_t path_waits = 0;
+  // The lanes of a wavefront leave this loop together: code after a loop runs
+  // once its last lane is out, and a lane that is done must give its path
+  // array back while others may still wait for it.  The ballot keeps the
+  // loop whole (a lane's own `result < 0` as the condition would let the
+  // compiler move the giving back behind it).
+  while (__builtin_amdgcn_ballot_w64(result < 0) != 0ull) {
+    if (result < 0) {
+      if (++iters > spin_limit) {
+        result = CKPP_RETRY;
+        spun = true;
+      } else if (state == DIRECT) {
+        const bool retry_displace = dretries < kDisplaceRetries;
+        const int r = insert_direct<TIMED>(bk, key, word, f, h, log2b, seed, plain, now,
+                                           retry_displace, pair);
+        if (r >= 0)
+          result = r;
+        else if (r == kNeedPath)
+          state = WALK;
+        else if (r == kDisplaceBusy)
+          ++dretries;  // DIRECT again
+      } else if (state == WALK) {
+        if (walks >= kMaxWalks) {
+          result = CKPP_FAILED;
+        } else if (!paths.take(path)) {
+          --iters;
+          if (++path_waits > kMaxRetryLimit) {
+            result = CKPP_RETRY;
+            spun = true;
+          }
+        } else {
+          const int L = walk(bk, f.p, h ^ ((uint64_t)walks * kWalkSalt), max_kicks, plain,
+                             path, &last);
+          ++walks;
+          if (L <= 0) {
+            result = CKPP_FAILED;
+          } else {
+            len = (uint32_t)L;
+            next = len;
+            state = MOVE;
+            // a short path in one critical section; step by step if a lock is
+            // held (then nothing was moved)
+            if (len <= kSectionPath &&
+                apply_path(bk, path, len, last, log2b, seed, plain) != kBusy)
+              state = DIRECT;
+          }
+        }
       } else {
-        len = (uint32_t)L;
-        next = len;
-        state = MOVE;
-        // a short path in one critical section; step by step if a lock is
-        // held (then nothing was moved)
-        if (len <= kSectionPath &&
-            apply_path(bk, path, len, last, log2b, seed, plain) != kBusy)
+        const uint32_t e = path[next - 1];
+        const uint32_t x = e & kPathBucketMask, s = e >> kPathSlotShift;
+        const uint32_t y = (next == len) ? last : (path[next] & kPathBucketMask);
+        const int r = move_entry(bk, x, s, y, log2b, seed, plain);
+        if (r == 1) {
+          if (--next == 0) state = DIRECT;
+        } else if (r == 0) {
           state = DIRECT;
-      }
-    } else {
-      const uint32_t e = path[next - 1];
-      const uint32_t x = e & kPathBucketMask, s = e >> kPathSlotShift;
-      const uint32_t y = (next == len) ? last : (path[next] & kPathBucketMask);
-      const int r = move_entry(bk, x, s, y, log2b, seed, plain);
-      if (r == 1) {
-        if (--next == 0) state = DIRECT;
-      } else if (r == 0) {
-        state = DIRECT;
+        }
       }
     }
+    if (result >= 0) paths.give();
   }
   return InsertOutcome{result, spun};
 }
