@@ -261,11 +261,6 @@ __device__ __forceinline__ uint32_t nth_bit(uint32_t m, uint32_t k) {
   return (uint32_t)__builtin_ctz(m);
 }
 
-__device__ __forceinline__ uint64_t load_relaxed(const uint8_t *p) {
-  return __hip_atomic_load((const Global<uint64_t> *)p, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // The paths that few keys take (displacements, the walk, a move, lazy
 // removal) are kept out of line: inlined, they raise the register count and
 // slow the direct path every key takes (measured: 2^24 build to load 0.95 in
@@ -334,38 +329,6 @@ __device__ __attribute__((noinline)) bool remove_expired(uint8_t *bk, Pair &P, i
   return true;
 }
 
-// Moves the entry of slot s of bucket x into the free slot fs of its other
-// bucket y (both locked), with the filter maintenance of a cuckoo move
-// (Sec. 4.1): an entry leaving its primary x adds its two bits to x's
-// filter and 1 to x's moved counter; an entry going home to y takes 1 off
-// y's counter and empties y's filter when it reaches zero.  The metadata
-// words are read and written in memory.
-__device__ void move_locked(uint8_t *bk, uint32_t x, uint32_t s, uint32_t y, uint32_t fs,
-                            uint32_t log2b, uint64_t seed, bool plain) {
-  const uint32_t mx = *meta_ptr(bk, x), my = *meta_ptr(bk, y);
-  const uint4 k = key_at(bk, x, s);
-  const uint64_t w = *value_ptr(bk, x, s);
-  const uint32_t tag = tag_ptr(bk, x)[s];
-  const bool guest = (meta_sec(mx) >> s) & 1u;  // in its secondary x: y is its home
-  write_entry(bk, y, fs, k, w, tag, x);
-  uint32_t moved_x = meta_moved(mx), moved_y = meta_moved(my);
-  if (!plain) {
-    if (guest) {
-      if (moved_y > 0u) {
-        moved_y -= 1u;
-        if (moved_y == 0u) *bloom_ptr(bk, y) = 0ull;
-      }
-    } else {
-      *bloom_ptr(bk, x) |= key_fields(key_hash(k, seed), log2b).bloom_bits;
-      moved_x += 1u;
-    }
-  }
-  const uint32_t fb = 1u << fs, sb = 1u << s;
-  *meta_ptr(bk, y) = make_meta(moved_y, meta_busy(my) | fb,
-                               guest ? (meta_sec(my) & ~fb) : (meta_sec(my) | fb));
-  *meta_ptr(bk, x) = make_meta(moved_x, meta_busy(mx) & ~sb, meta_sec(mx) & ~sb);
-}
-
 // Entries of a full bucket that may move (an entry leaving its primary
 // must not overflow that primary's moved counter).
 __device__ __forceinline__ uint32_t movable(uint32_t meta, bool plain) {
@@ -374,29 +337,23 @@ __device__ __forceinline__ uint32_t movable(uint32_t meta, bool plain) {
   return c;
 }
 
-// The other buckets of bucket b's entries and, for the entries in `cand`,
-// which of those buckets have a free slot (their metadata words loaded
-// together, without locks).  Every slot's load is issued, a non-candidate
-// reading bucket b itself, so that no load waits inside a branch: two round
-// trips in all.
-__device__ __forceinline__ uint32_t room_of(const uint8_t *bk, uint32_t b, uint32_t cand,
-                                            uint32_t (&other)[kSlots]) {
-#pragma unroll
-  for (uint32_t w = 0; w < 4; ++w) {
-    const uint64_t o = load_relaxed(bucket_ptr(bk, b) + kOtherOffset + 8 * w);
-    other[2 * w] = (uint32_t)o;
-    other[2 * w + 1] = (uint32_t)(o >> 32);
-  }
-  uint32_t om[kSlots];
-#pragma unroll
-  for (uint32_t s = 0; s < kSlots; ++s)
-    om[s] = (uint32_t)load_relaxed(bucket_ptr(bk, ((cand >> s) & 1u) ? other[s] : b) +
-                                   kMetaOffset);
-  uint32_t room = 0;
-#pragma unroll
-  for (uint32_t s = 0; s < kSlots; ++s)
-    if (((cand >> s) & 1u) && meta_busy(om[s]) != 0xffu) room |= 1u << s;
-  return room;
+// The metadata word of bucket b, read without its lock.
+__device__ __forceinline__ uint32_t peek_meta(const uint8_t *bk, uint32_t b) {
+  return __hip_atomic_load((const Global<uint32_t> *)(bucket_ptr(bk, b) + kMetaOffset),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The other buckets of bucket b's entries.
+__device__ __forceinline__ void read_other(uint8_t *bk, uint32_t b, uint32_t (&other)[kSlots]) {
+  const uint4 lo = quarter(bk, b, kOtherOffset), hi = quarter(bk, b, kOtherOffset + 16u);
+  other[0] = lo.x;
+  other[1] = lo.y;
+  other[2] = lo.z;
+  other[3] = lo.w;
+  other[4] = hi.x;
+  other[5] = hi.y;
+  other[6] = hi.z;
+  other[7] = hi.w;
 }
 
 // a[i] for a small array indexed by a value known only at run time, as an
@@ -410,82 +367,175 @@ __device__ __forceinline__ uint32_t pick_slot(const uint32_t (&a)[kSlots], uint3
   return r;
 }
 
-// Takes the lock of bucket b unless the caller holds it already.
-__device__ __forceinline__ bool lock_extra(uint8_t *bk, uint32_t b, const KeyFields &f) {
-  return b == f.p || b == f.a || try_lock(bk, b);
-}
-__device__ __forceinline__ void unlock_extra(uint8_t *bk, uint32_t b, const KeyFields &f) {
-  if (b != f.p && b != f.a) unlock(bk, b);
+// The entries of bucket b (its other[] in `other`) among `cand` whose other
+// bucket has a free slot, by those buckets' metadata words, read without
+// locks.  Every slot's load is issued, a non-candidate reading bucket b
+// itself, so that no load waits inside a branch: one round trip.
+__device__ __forceinline__ uint32_t with_room(const uint8_t *bk, uint32_t b, uint32_t cand,
+                                              const uint32_t (&other)[kSlots]) {
+  uint32_t om[kSlots];
+#pragma unroll
+  for (uint32_t s = 0; s < kSlots; ++s) om[s] = peek_meta(bk, ((cand >> s) & 1u) ? other[s] : b);
+  uint32_t room = 0;
+#pragma unroll
+  for (uint32_t s = 0; s < kSlots; ++s)
+    if (((cand >> s) & 1u) && meta_busy(om[s]) != 0xffu) room |= 1u << s;
+  return room;
 }
 
-// Cuckoo displacements done inside DIRECT, under the locks of the key's two
-// buckets, when the primary p is full: the walk's lookahead from p, one
-// level and, if no entry of p can move at once, two.  One step: an entry v
-// of p whose other bucket y has a free slot (preferably one going home)
-// moves there.  Two steps: an entry of some y1 = other(v) moves on to its
-// own other bucket y2, which has a free slot, and v takes its place.  The
-// buckets beyond p and a are locked here (never waited on), the path is
-// re-checked under the locks, the moves are applied last to first with the
-// filter maintenance of Sec. 4.1, and the key takes v's slot in p.  Almost
-// every key that needs a cuckoo path needs at most two displacements, which
-// then cost one critical section instead of a walk, one locked move per
-// displacement and a second DIRECT step.  mp: p's meta word read under the
-// lock.  Returns true when the key was placed; false, with nothing changed,
-// when no such path exists (the caller falls back to the walk); kBusy,
-// with nothing changed, when a bucket beyond the pair is locked by another
+// As with_room, for a search that needs one such entry: four at a time, the
+// entries that sit in their secondary first, then those of the slots in
+// `half`, then the rest; stops at the first four that hold one.
+__device__ __forceinline__ uint32_t some_with_room(const uint8_t *bk, uint32_t b, uint32_t cand,
+                                                   uint32_t sec, uint32_t half,
+                                                   const uint32_t (&other)[kSlots]) {
+  uint32_t room = 0u;
+  for (uint32_t left = cand; left != 0u && room == 0u;) {
+    uint32_t s[4], om[4];
+#pragma unroll
+    for (uint32_t k = 0; k < 4u; ++k) {
+      const uint32_t g = left & sec, o = left & half;
+      const uint32_t from = g ? g : o ? o : left;
+      s[k] = from ? (uint32_t)__builtin_ctz(from) : kSlots;
+      if (from) left &= ~(from & (0u - from));
+      om[k] = peek_meta(bk, from ? pick_slot(other, s[k]) : b);
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < 4u; ++k)
+      if (s[k] < kSlots && meta_busy(om[k]) != 0xffu) room |= 1u << s[k];
+  }
+  return room;
+}
+
+// An entry.
+struct Slot {
+  uint4 key;
+  uint64_t word;
+  uint32_t tag;
+};
+__device__ __forceinline__ Slot read_slot(uint8_t *bk, uint32_t b, uint32_t s) {
+  return Slot{key_at(bk, b, s), value_ptr(bk, b, s)[0], tag_ptr(bk, b)[s]};
+}
+
+// The filter and metadata of a locked bucket as a step changes them; the
+// filter is written where it changes, the metadata with the unlock.
+struct Work {
+  uint32_t b;
+  uint32_t moved, busy, sec;
+  uint64_t bloom;
+  bool filter;  // the filter has changed
+};
+__device__ __forceinline__ Work work_of(uint32_t b, uint4 q1) {
+  return Work{b, meta_moved(q1.z), meta_busy(q1.z), meta_sec(q1.z),
+              (uint64_t)q1.x | ((uint64_t)q1.y << 32), false};
+}
+__device__ __forceinline__ void finish_filter(uint8_t *bk, const Work &W) {
+  if (W.filter) *bloom_ptr(bk, W.b) = W.bloom;
+}
+__device__ __forceinline__ void finish_meta(uint8_t *bk, const Work &W) {
+  unlock_meta(bk, W.b, make_meta(W.moved, W.busy, W.sec));
+}
+
+// Entry e moves from slot s of X to slot fs of its other bucket Y (both
+// locked), with the filter maintenance of a cuckoo move (Sec. 4.1): an entry
+// leaving its primary X adds its two bits to X's filter and 1 to X's moved
+// counter; an entry going home to Y takes 1 off Y's counter and empties Y's
+// filter when it reaches zero.  X's slot is left busy: the caller puts
+// another entry there.
+__device__ __forceinline__ void move_slot(uint8_t *bk, Work &X, uint32_t s, const Slot &e,
+                                          Work &Y, uint32_t fs, uint32_t log2b, uint64_t seed,
+                                          bool plain) {
+  const bool guest = (X.sec >> s) & 1u;  // in its secondary X: Y is its home
+  write_entry(bk, Y.b, fs, e.key, e.word, e.tag, X.b);
+  Y.busy |= 1u << fs;
+  Y.sec = guest ? (Y.sec & ~(1u << fs)) : (Y.sec | (1u << fs));
+  if (plain) return;
+  if (guest) {
+    if (Y.moved > 0u && --Y.moved == 0u) {
+      Y.bloom = 0ull;
+      Y.filter = true;
+    }
+  } else {
+    X.bloom |= key_fields(key_hash(e.key, seed), log2b).bloom_bits;
+    X.moved += 1u;
+    X.filter = true;
+  }
+}
+
+// Takes the lock of bucket b unless the caller holds it already (own: the
+// bucket beside p whose lock is held, or kNoBucket).
+__device__ __forceinline__ bool lock_extra(uint8_t *bk, uint32_t b, uint32_t own) {
+  return b == own || try_lock(bk, b);
+}
+__device__ __forceinline__ void unlock_extra(uint8_t *bk, uint32_t b, uint32_t own) {
+  if (b != own) unlock(bk, b);
+}
+
+// Cuckoo displacements done inside DIRECT, under the lock of the key's full
+// primary p: the walk's lookahead from p, one level and, if no entry of p can
+// move at once, two.  One step: an entry v of p whose other bucket y1 has a
+// free slot (preferably one going home) moves there.  Two steps: an entry t
+// of some y1 = other(v) moves on to its own other bucket y2, which has a free
+// slot, and v takes its place.  The buckets beyond p (and `own`, the key's
+// secondary when the caller holds its lock, else kNoBucket) are locked here
+// (never waited on), the path is re-checked under the locks, the moves are
+// applied last to first with the filter maintenance of Sec. 4.1, and the key
+// takes v's slot in p.  Almost every key that needs a cuckoo path needs at
+// most two displacements, which then cost one critical section instead of a
+// walk, one locked move per displacement and a second DIRECT step.
+//
+// Like the direct step this is bound by its memory requests, so the entries
+// looked at and the words written are as few as the step allows: the entries
+// are looked at four at a time (some_with_room), p's filter and metadata are
+// those read under its lock (q1), and each bucket's metadata is written once,
+// with its unlock; when the secondary looks full without its lock, that lock
+// is not taken.  Measured on MI355X, keys that bring 2^22 buckets from load
+// 0.85 to 0.9 at 1.94 -> 2.58 G/s, from 0.9 to 0.95 at 1.37 -> 1.77 G/s (all
+// eight entries looked at, metadata read and written around each move).
+//
+// Returns 1 when the key was placed
+// (every lock is dropped); 0, with nothing changed and the caller's locks
+// still held, when no such path exists (the caller falls back to the walk);
+// kBusy, likewise, when a bucket beyond the caller's is locked by another
 // lane or its state changed before the lock (the caller may retry DIRECT:
-// another lane's move is brief, and a retry costs a few round trips where
-// the walk costs tens).
-__device__ __attribute__((noinline)) int displace_and_place(uint8_t *bk, uint32_t log2b, uint64_t seed, bool plain,
-                                   const KeyFields &f, uint64_t h, uint4 key, uint64_t word,
-                                   uint32_t mp) {
-  const uint32_t cand = movable(mp, plain), sec = meta_sec(mp), p = f.p;
+// another lane's move is brief, and a retry costs a few round trips where the
+// walk costs tens).
+__device__ __attribute__((noinline)) int displace_and_place(
+    uint8_t *bk, uint32_t log2b, uint64_t seed, bool plain, uint32_t p, uint32_t a, uint32_t own,
+    uint32_t tag, uint64_t h, uint4 key, uint64_t word, uint4 q1) {
+  const uint32_t mp = q1.z, cand = movable(mp, plain), sec = meta_sec(mp);
   uint32_t other[kSlots];
-  const uint32_t room = room_of(bk, p, cand, other);
+  read_other(bk, p, other);
   uint32_t v = kSlots, y1 = kNoBucket, t = kSlots, y2 = kNoBucket;
+  const uint64_t draw = mix64(h ^ kDisplaceSalt);
+  const uint32_t half = draw & 1u ? 0xf0u : 0x0fu;
+  const uint32_t room = some_with_room(bk, p, cand, sec, half, other);
   if (room) {
     const uint32_t pick = (room & sec) ? (room & sec) : room;
-    v = nth_bit(pick, random_below(mix64(h ^ kDisplaceSalt),
-                                   (uint32_t)__builtin_popcount(pick)));
+    v = nth_bit(pick, random_below(draw, (uint32_t)__builtin_popcount(pick)));
     y1 = pick_slot(other, v);
   } else {
     // second level, one candidate at a time in the order of the choice
     // (entries of p going home first), two round trips each: the metadata
     // word and other[] of the candidate's other bucket y1, then the
     // metadata words of y1's entries' other buckets, all of a round trip's
-    // loads issued together (a non-movable slot reads y1 itself, so that
-    // none waits inside a branch).  The first candidate whose y1 has an
-    // entry that can move on to a bucket with a free slot wins (an entry of
-    // y1 going home preferred); at the loads of the table's working loads
-    // that is nearly always the first one tried.  Searching every candidate
-    // at once takes 104 loads; measured on MI355X, one wavefront's lane
-    // spends some 20 us issuing them and choosing, against about 1 us for a
-    // candidate's two round trips.
+    // loads issued together.  The first candidate whose y1 has an entry that
+    // can move on to a bucket with a free slot wins (an entry of y1 going
+    // home preferred); at the loads of the table's working loads that is
+    // nearly always the first one tried.  Searching every candidate at once
+    // takes 104 loads; measured on MI355X, one wavefront's lane spends some
+    // 20 us issuing them and choosing, against about 1 us for a candidate's
+    // two round trips.
     for (uint32_t order = 0; order < 2 && t == kSlots; ++order) {
       for (uint32_t c = cand & (order ? ~sec : sec); c && t == kSlots; c &= c - 1u) {
         const uint32_t s = (uint32_t)__builtin_ctz(c);
         const uint32_t b1 = pick_slot(other, s);
-        const uint8_t *base1 = bucket_ptr(bk, b1);
-        const uint32_t m1 = (uint32_t)load_relaxed(base1 + kMetaOffset);
+        const uint32_t m1 = peek_meta(bk, b1);
         uint32_t o1[kSlots];
-#pragma unroll
-        for (uint32_t w = 0; w < 4; ++w) {
-          const uint64_t o = load_relaxed(base1 + kOtherOffset + 8 * w);
-          o1[2 * w] = (uint32_t)o;
-          o1[2 * w + 1] = (uint32_t)(o >> 32);
-        }
-        const uint32_t mv = movable(m1, plain);
-        uint32_t om[kSlots];
-#pragma unroll
-        for (uint32_t u = 0; u < kSlots; ++u)
-          om[u] = (uint32_t)load_relaxed(bucket_ptr(bk, ((mv >> u) & 1u) ? o1[u] : b1) +
-                                         kMetaOffset);
-        uint32_t r = 0u;
-#pragma unroll
-        for (uint32_t u = 0; u < kSlots; ++u)
-          if (((mv >> u) & 1u) && meta_busy(om[u]) != 0xffu) r |= 1u << u;
+        read_other(bk, b1, o1);
+        const uint32_t sc = meta_sec(m1);
+        const uint32_t r = some_with_room(bk, b1, movable(m1, plain), sc, half, o1);
         if (r) {
-          const uint32_t sc = meta_sec(m1);
           const uint32_t pick = (r & sc) ? (r & sc) : r;
           v = s;
           t = (uint32_t)__builtin_ctz(pick);
@@ -496,46 +546,55 @@ __device__ __attribute__((noinline)) int displace_and_place(uint8_t *bk, uint32_
     }
     if (t == kSlots) return 0;
   }
-  // lock the buckets beyond p and a (both compare-and-swaps issued
-  // together: a failure here is not retried but falls back to the walk, so
-  // it cannot repeat in lockstep), then re-check the path under the locks
-  const bool ok1 = lock_extra(bk, y1, f);
-  const bool ok2 = y2 == kNoBucket || lock_extra(bk, y2, f);
+  // lock the buckets beyond the caller's (both compare-and-swaps issued
+  // together: a failure here is not retried but falls back to DIRECT, a few
+  // times, and the walk, so it cannot repeat in lockstep), then re-check the
+  // path under the locks
+  const bool two = y2 != kNoBucket;
+  const bool ok1 = lock_extra(bk, y1, own);
+  const bool ok2 = !two || lock_extra(bk, y2, own);
   if (!(ok1 && ok2)) {
-    if (ok1) unlock_extra(bk, y1, f);
-    if (ok2 && y2 != kNoBucket) unlock_extra(bk, y2, f);
+    if (ok1) unlock_extra(bk, y1, own);
+    if (ok2 && two) unlock_extra(bk, y2, own);
     return kBusy;
   }
   section_begin();
-  bool done = false;
-  const uint32_t my1 = *meta_ptr(bk, y1);
-  if (y2 == kNoBucket) {
-    if (meta_busy(my1) != 0xffu) {
-      move_locked(bk, f.p, v, y1, (uint32_t)__builtin_ctz(~meta_busy(my1) & 0xffu), log2b, seed,
-                  plain);
-      done = true;
-    }
+  Work P = work_of(p, q1);
+  Work Y1 = work_of(y1, quarter(bk, y1, 16u));
+  Work Y2{kNoBucket, 0u, 0u, 0u, 0ull, false};
+  const Slot ev = read_slot(bk, p, v);
+  uint32_t fs = t;
+  bool still;
+  if (two) {
+    Y2 = work_of(y2, quarter(bk, y2, 16u));
+    const Slot et = read_slot(bk, y1, t);
+    const uint32_t ot = other_ptr(bk, y1)[t];
+    still = ((Y1.busy >> t) & 1u) && ot == y2 && Y2.busy != 0xffu &&
+            (plain || Y1.moved < 0xffffu || ((Y1.sec >> t) & 1u));
+    if (still)
+      move_slot(bk, Y1, t, et, Y2, (uint32_t)__builtin_ctz(~Y2.busy & 0xffu), log2b, seed, plain);
   } else {
-    const uint32_t my2 = *meta_ptr(bk, y2);
-    const bool still = ((meta_busy(my1) >> t) & 1u) && other_ptr(bk, y1)[t] == y2 &&
-                       ((movable(my1, plain) >> t) & 1u) && meta_busy(my2) != 0xffu;
-    if (still) {
-      move_locked(bk, y1, t, y2, (uint32_t)__builtin_ctz(~meta_busy(my2) & 0xffu), log2b, seed,
-                  plain);
-      move_locked(bk, f.p, v, y1, t, log2b, seed, plain);
-      done = true;
-    }
+    still = Y1.busy != 0xffu;
+    fs = (uint32_t)__builtin_ctz(~Y1.busy & 0xffu);
   }
-  if (done) {
-    // the key takes slot v of p, its primary
-    write_entry(bk, f.p, v, key, word, f.tag, f.a);
-    const uint32_t m = *meta_ptr(bk, f.p), vb = 1u << v;
-    *meta_ptr(bk, f.p) = make_meta(meta_moved(m), meta_busy(m) | vb, meta_sec(m) & ~vb);
+  if (!still) {
+    if (two) unlock_extra(bk, y2, own);
+    unlock_extra(bk, y1, own);
+    return kBusy;
   }
+  move_slot(bk, P, v, ev, Y1, fs, log2b, seed, plain);
+  // the key takes slot v of p, its primary
+  write_entry(bk, p, v, key, word, tag, a);
+  P.sec &= ~(1u << v);
+  finish_filter(bk, P);
+  finish_filter(bk, Y1);
+  if (two) finish_filter(bk, Y2);
   section_end();
-  if (y2 != kNoBucket) unlock_extra(bk, y2, f);
-  unlock_extra(bk, y1, f);
-  return done ? 1 : kBusy;
+  finish_meta(bk, P);
+  finish_meta(bk, Y1);
+  if (two) finish_meta(bk, Y2);
+  if (own != kNoBucket && own != y1 && own != y2) unlock(bk, own);
+  return 1;
 }
 
 // Takes the locks a step of a key with buckets p and a starts with: p's
@@ -600,16 +659,15 @@ __device__ __forceinline__ int insert_primary(uint8_t *bk, uint4 key, uint64_t w
   return CKPP_INSERTED;
 }
 
-// The DIRECT step of an absent key under the locks of both its buckets: the
-// lowest free slot of p, else of a; with timers also a slot whose entry has
-// expired, after the free ones of its bucket; else displacements.  Drops
-// the locks.
+// The DIRECT step of an absent key under the locks of both its buckets (q1:
+// p's filter and metadata): the lowest free slot of p, else of a; with timers
+// also a slot whose entry has expired, after the free ones of its bucket;
+// else displacements.  Drops the locks.
 template <bool TIMED>
 __device__ __forceinline__ int insert_pair(uint8_t *bk, uint4 key, uint64_t word,
                                            const KeyFields &f, uint64_t h, uint32_t log2b,
                                            uint64_t seed, bool plain, uint32_t now,
-                                           bool retry_displace, Pair &P) {
-  const uint32_t mp = P.meta[0];
+                                           bool retry_displace, Pair &P, uint4 q1) {
   int r = kNeedPath;
   for (int xi = 0; xi < 2 && r == kNeedPath; ++xi) {
     if (xi == 1 && !plain && meta_moved(P.meta[0]) >= 0xffffu) break;
@@ -653,9 +711,10 @@ __device__ __forceinline__ int insert_pair(uint8_t *bk, uint4 key, uint64_t word
     return r;
   }
   if (r == kNeedPath) {
-    const int d = displace_and_place(bk, log2b, seed, plain, f, h, key, word, mp);
-    if (d == 1) r = CKPP_INSERTED;
-    else if (d == kBusy && retry_displace) r = kDisplaceBusy;
+    const int d = displace_and_place(bk, log2b, seed, plain, f.p, f.a, f.a, f.tag, h, key, word,
+                                     q1);
+    if (d == 1) return CKPP_INSERTED;
+    if (d == kBusy && retry_displace) r = kDisplaceBusy;
   }
   unlock_two(bk, f.p, f.a);
   return r;
@@ -694,18 +753,33 @@ __device__ int insert_direct(uint8_t *bk, uint4 key, uint64_t word, const KeyFie
     if (both) unlock(bk, f.a);
     return r;
   }
+  const bool pass = plain || bloom_pass(hp.q1, f.bloom_bits);
+  if (!TIMED && !both && !pass && meta_busy(peek_meta(bk, f.a)) == 0xffu) {
+    // the key is absent, p is full and a looked full without its lock:
+    // displacements need p's lock alone
+    const int d = displace_and_place(bk, log2b, seed, plain, f.p, f.a, kNoBucket, f.tag, h, key,
+                                     word, hp.q1);
+    if (d == 1) return CKPP_INSERTED;
+    unlock(bk, f.p);
+    return d == kBusy && retry_displace ? kDisplaceBusy : kNeedPath;
+  }
   if (!lock_second(bk, f, pair)) return kBusy;
-  const Head ha = read_head(bk, f.a);
-  if (plain || bloom_pass(hp.q1, f.bloom_bits)) {
+  uint4 qa;  // a's filter and metadata; its tags matter only to a key it may hold
+  if (pass) {
+    const Head ha = read_head(bk, f.a);
     const int s = find_slot(bk, f.a, ha, key, f.tag);
     if (s >= 0) {
       const int u = update_entry<TIMED>(bk, f.a, (uint32_t)s, word, now);
       unlock_two(bk, f.p, f.a);
       return u;
     }
+    qa = ha.q1;
+  } else {
+    qa = quarter(bk, f.a, 16u);
   }
-  Pair P{{f.p, f.a}, {hp.q1.z, ha.q1.z}, (uint64_t)hp.q1.x | ((uint64_t)hp.q1.y << 32)};
-  return insert_pair<TIMED>(bk, key, word, f, h, log2b, seed, plain, now, retry_displace, P);
+  Pair P{{f.p, f.a}, {hp.q1.z, qa.z}, (uint64_t)hp.q1.x | ((uint64_t)hp.q1.y << 32)};
+  return insert_pair<TIMED>(bk, key, word, f, h, log2b, seed, plain, now, retry_displace, P,
+                            hp.q1);
 }
 
 // A cuckoo path's entries in memory (bucket | slot << 29), in groups of
@@ -764,36 +838,20 @@ __device__ __forceinline__ uint32_t path_slots(PathRef path, uint32_t n, uint32_
 // path[i] holds bucket | slot << 29 of the i-th victim; *last receives the
 // bucket with a free slot that ends the path.  Returns the path length, or
 // -1.
-__device__ __attribute__((noinline)) int walk(const uint8_t *bk, uint32_t start, uint64_t rbase, uint32_t max_kicks,
+__device__ __attribute__((noinline)) int walk(uint8_t *bk, uint32_t start, uint64_t rbase, uint32_t max_kicks,
                     bool plain, PathRef path, uint32_t *last) {
   uint32_t cur = start, prev = kNoBucket;
   for (uint32_t step = 0; step < max_kicks; ++step) {
-    const uint8_t *base = bucket_ptr(bk, cur);
-    const uint32_t meta = (uint32_t)load_relaxed(base + kMetaOffset);
+    const uint32_t meta = peek_meta(bk, cur);
     uint32_t other[kSlots];
-#pragma unroll
-    for (uint32_t w = 0; w < 4; ++w) {
-      const uint64_t o = load_relaxed(base + kOtherOffset + 8 * w);
-      other[2 * w] = (uint32_t)o;
-      other[2 * w + 1] = (uint32_t)(o >> 32);
-    }
+    read_other(bk, cur, other);
     const uint32_t used = path_slots(path, step, cur);
     const uint32_t sec = meta_sec(meta);
     uint32_t cand = meta_busy(meta) & ~used;
     if (!plain && meta_moved(meta) >= 0xffffu) cand &= sec;  // no owner may leave
     if (!cand) return -1;
-    // lookahead: which candidates' other buckets have a free slot (every
-    // slot's load issued, a non-candidate reading the current bucket, so
-    // that all are in flight together)
-    uint32_t om[kSlots];
-#pragma unroll
-    for (uint32_t s = 0; s < kSlots; ++s)
-      om[s] = (uint32_t)load_relaxed(bucket_ptr(bk, ((cand >> s) & 1u) ? other[s] : cur) +
-                                     kMetaOffset);
-    uint32_t room = 0;
-#pragma unroll
-    for (uint32_t s = 0; s < kSlots; ++s)
-      if (((cand >> s) & 1u) && meta_busy(om[s]) != 0xffu) room |= 1u << s;
+    // lookahead: which candidates' other buckets have a free slot
+    const uint32_t room = with_room(bk, cur, cand, other);
     const uint64_t r = mix64(rbase + (uint64_t)(step + 1) * kGolden);
     if (room) {
       const uint32_t pick = (room & sec) ? (room & sec) : room;
