@@ -25,7 +25,8 @@
  *    CKPP_OK.  A failed kernel launch returns CKPP_EDEVICE.
  *  - The table's device memory is owned by the library: 256 * 2^B bytes
  *    (32 bytes per slot: bucket b holds its metadata and the keys and values
- *    of its 8 slots in two 128-byte lines), plus a small working area.
+ *    of its 8 slots in two 128-byte lines), plus working areas that inserts
+ *    allocate on first use (ckpp_insert_batch).
  *
  * Image layout (the interchange format of export/import, independent of the
  * device layout; fixed, little-endian):
@@ -148,7 +149,12 @@ int ckpp_clear(ckpp_table *t, void *stream);
  * max_kicks bytes, at most 2^17 of them and at most 1/8 of the table's
  * device memory, but at least 4096; keys that search a path beyond that many
  * at once take turns.  (A first insert on a stream under capture takes it
- * from the device's stream-ordered memory pool.)  Two insert batches of one table must therefore not
+ * from the device's stream-ordered memory pool.)  A dense batch, two keys per
+ * bucket or more, is binned by bucket first, in a second buffer of the
+ * table's own: half of the table's device memory, between 4 and 512 MiB,
+ * allocated on the first such batch and freed with the table (without it, on
+ * a stream under capture or out of memory, the batch runs key by key, with
+ * the same results).  Two insert batches of one table must therefore not
  * overlap in time (order them on one stream).
  * Errors: CKPP_EINVAL (null table/keys/values with n > 0, misaligned keys),
  * CKPP_ENOMEM (scratch allocation failed). */

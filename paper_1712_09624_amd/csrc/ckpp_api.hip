@@ -240,6 +240,7 @@ int ckpp_destroy(ckpp_table *t) {
   (void)hipFree(t->d_table);
   (void)hipFree(t->d_stats);
   if (t->d_own_paths) (void)hipFree(t->d_own_paths);
+  if (t->d_bulk) (void)hipFree(t->d_bulk);
   delete t;
   return CKPP_OK;
 }

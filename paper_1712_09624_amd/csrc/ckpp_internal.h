@@ -17,6 +17,7 @@ struct ckpp_table {
   uint32_t *d_own_paths;    // the table's own cuckoo-path scratch (own_paths
                             // arrays), allocated on the first insert
   uint32_t own_paths;
+  uint8_t *d_bulk;      // bins of dense insert batches, allocated on the first
   uint64_t *d_stats;    // device accumulator of ckpp_stats_t
   uint32_t retry_limit; // attempts per key on contended locks (ckpp_set_retry_limit)
   ckpp_launch_t lookup_launch;
@@ -40,6 +41,27 @@ inline __host__ __device__ uint32_t path_words(uint32_t max_kicks) {
 // launch while it stays within 1/kOwnPathShare of the table's own memory.
 constexpr uint32_t kOwnPathsMin = 4096;
 constexpr uint64_t kOwnPathShare = 8;
+
+// Dense insert batches (ckpp_bulk.hip).  Status of a key that waits for the
+// second stage.
+constexpr uint8_t kInsertPending = 0xffu;
+// The batches that take that way hold at least kMinBulkKeys keys and two per
+// bucket of the table.  Measured on MI355X, one key per bucket, this way and
+// the other: 2^18 buckets 32 and 38 us from empty, 53 and 53 us from load
+// 0.5; 2^20 buckets 103 and 103, 143 and 132; 2^22 buckets 518 and 643, 665
+// and 771.  Tables of 2^24 buckets have so many bins that a block writes only
+// two records to each: three keys per bucket (one: 2829 and 2523 us, 3248 and
+// 2926; four, from load 0.5: 15.2 and 18.6 ms).  Larger tables have more bins
+// than fit the counters in LDS.
+constexpr uint64_t kMinBulkKeys = 4096;
+constexpr uint32_t kMaxBulkLog2Buckets = 24;
+inline uint64_t min_bulk_keys(uint32_t log2b) {
+  const uint64_t n = (log2b < 24u ? 2ull : 3ull) << log2b;
+  return n < kMinBulkKeys ? kMinBulkKeys : n;
+}
+// The bins' buffer: half of the table's memory within these bounds.
+constexpr uint64_t kMinBulkBytes = 4ull << 20;
+constexpr uint64_t kMaxBulkBytes = 512ull << 20;
 
 // One work item of a plan: lookups [start, start + count) of the
 // concatenated key batch, all of one table, with that table's parameters
@@ -109,6 +131,12 @@ hipError_t launch_plan(const PlanItem *d_items, uint32_t nitems, uint32_t *d_ctr
 hipError_t launch_insert(const ckpp_table *t, const void *d_keys, const uint64_t *d_values,
                          const uint16_t *d_expiry, const TimerArgs *timers, uint64_t n,
                          uint8_t *d_status, uint64_t *d_nfailed, hipStream_t s);
+// The first stage of a dense batch: places the keys that their primary bucket
+// decides, writes every key's status (kInsertPending for the others).  *taken:
+// whether the batch is one for this way (else nothing was done).
+hipError_t bulk_insert_primary(ckpp_table *t, const void *d_keys, const uint64_t *d_values,
+                               const uint16_t *d_expiry, const TimerArgs *timers, uint64_t n,
+                               uint8_t *d_status, hipStream_t s, bool *taken);
 hipError_t launch_delete(const ckpp_table *t, const void *d_keys, uint64_t n,
                          const TimerArgs *timers, uint8_t *d_found, hipStream_t s);
 // The insert without any allocation (ckpp_insert_batch_noalloc): returns a

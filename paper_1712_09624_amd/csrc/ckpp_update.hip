@@ -158,6 +158,54 @@ __global__ void __launch_bounds__(256) insert_lanes(InsertArgs A) {
   }
 }
 
+// The second stage of a dense batch: the keys whose status is kInsertPending,
+// gathered and run 64 at a time as in insert_lanes.  A wavefront reads `tile`
+// statuses at a time (at most kTile): few of them on a small batch, so that
+// its slow keys spread over every wavefront.
+constexpr uint32_t kTile = 256;
+
+template <bool TIMED>
+__global__ void __launch_bounds__(256) insert_marked(InsertArgs A, uint32_t tile) {
+  __shared__ unsigned long long s_held[4];
+  __shared__ uint64_t s_wait[4][64 + kTile];
+  if (threadIdx.x < 4u) s_held[threadIdx.x] = 0ull;
+  __syncthreads();
+  const uint32_t lane = threadIdx.x & 63u;
+  const WavePath paths = wave_paths(A, s_held);
+  uint64_t *wait = s_wait[threadIdx.x >> 6];
+  uint32_t waiting = 0u;
+  const uint64_t wave = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  const uint64_t stride = ((uint64_t)gridDim.x * blockDim.x >> 6) * tile;
+  for (uint64_t i0 = wave * tile; i0 < A.n; i0 += stride) {
+    const uint64_t end = i0 + tile < A.n ? i0 + tile : A.n;
+    uint8_t st[kTile / 64];
+#pragma unroll
+    for (uint32_t k = 0; k < kTile / 64u; ++k) {
+      const uint64_t i = i0 + 64u * k + lane;
+      st[k] = A.status[i < end ? i : i0];
+      if (i >= end) st[k] = 0u;
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < kTile / 64u; ++k) {
+      const bool later = st[k] == kInsertPending;
+      const uint64_t m = __builtin_amdgcn_ballot_w64(later);
+      if (later)
+        wait[waiting + (uint32_t)__builtin_popcountll(m & ((1ull << lane) - 1ull))] =
+            i0 + 64u * k + lane;
+      waiting += (uint32_t)__builtin_popcountll(m);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    while (waiting >= 64u) {
+      waiting -= 64u;
+      insert_key<TIMED>(A, wait[waiting + lane], true, paths);
+    }
+  }
+  if (waiting) {
+    const bool ok = lane < waiting;
+    insert_key<TIMED>(A, ok ? wait[lane] : 0ull, ok, paths);
+  }
+}
+
 template <bool TIMED>
 __global__ void __launch_bounds__(256)
     delete_kernel(uint8_t *bk, const uint4 *__restrict__ keys, uint64_t n, uint32_t now,
@@ -207,18 +255,24 @@ namespace {
 // Launches an insert of A.n keys with `npaths` path arrays at A.paths
 // (npaths >= kMinPaths): one key per wavefront for few keys, else one lane
 // per key on at most t->path_lanes lanes and npaths wavefronts.
-hipError_t launch_insert_kernel(const ckpp_table *t, InsertArgs A, bool timed, uint64_t npaths,
-                                hipStream_t s) {
-  const bool spread = A.n <= kSpreadKeys && A.n <= npaths;
+// marked: only the keys whose status is kInsertPending.
+hipError_t launch_insert_kernel(const ckpp_table *t, InsertArgs A, bool timed, bool marked,
+                                uint64_t npaths, hipStream_t s) {
+  const bool spread = !marked && A.n <= kSpreadKeys && A.n <= npaths;
   const uint32_t block = 256, waves = block / 64u;
-  uint64_t lanes = spread ? 64u * A.n : A.n < t->path_lanes ? A.n : t->path_lanes;
+  uint64_t lanes = spread ? 64u * A.n : A.n < t->path_lanes && !marked ? A.n : t->path_lanes;
   if (lanes > 64u * npaths) lanes = 64u * npaths;
   uint64_t grid = (lanes + block - 1) / block;
   if (grid * waves > npaths) grid = npaths / waves;
   const uint64_t per_wave = npaths / (grid * waves);
   A.wave_paths = per_wave < 64u ? (uint32_t)per_wave : 64u;
   const dim3 g((uint32_t)grid), b(block);
-  if (timed) {
+  if (marked) {
+    uint32_t tile = kTile;
+    while (tile > 8u && (uint64_t)tile * waves * grid > A.n) tile /= 2u;
+    if (timed) hipLaunchKernelGGL(insert_marked<true>, g, b, 0, s, A, tile);
+    else hipLaunchKernelGGL(insert_marked<false>, g, b, 0, s, A, tile);
+  } else if (timed) {
     if (spread) hipLaunchKernelGGL(insert_spread<true>, g, b, 0, s, A);
     else hipLaunchKernelGGL(insert_lanes<true>, g, b, 0, s, A);
   } else {
@@ -275,7 +329,10 @@ hipError_t launch_insert(const ckpp_table *t, const void *d_keys, const uint64_t
   }
   const InsertArgs A = insert_args(t, d_keys, d_values, d_expiry, timers ? timers->now : 0u, n,
                                    paths, d_status, d_nfailed);
-  e = launch_insert_kernel(t, A, timers != nullptr, t->own_paths, s);
+  bool bulk = false;
+  e = bulk_insert_primary(tm, d_keys, d_values, d_expiry, timers, n, d_status, s, &bulk);
+  if (e == hipSuccess)
+    e = launch_insert_kernel(t, A, timers != nullptr, bulk, t->own_paths, s);
   if (!pooled) return e;
   const hipError_t f = hipFreeAsync(paths, s);
   return e != hipSuccess ? e : f;
@@ -314,7 +371,7 @@ int insert_noalloc(const ckpp_table *t, const void *d_keys, const uint64_t *d_va
   if (!paths) return CKPP_EDEVICE;
   const InsertArgs A =
       insert_args(t, d_keys, d_values, nullptr, 0u, n, paths, d_status, d_nfailed);
-  return dev_status(launch_insert_kernel(t, A, false, kScratchBytes / path_bytes, s));
+  return dev_status(launch_insert_kernel(t, A, false, false, kScratchBytes / path_bytes, s));
 }
 
 hipError_t launch_delete(const ckpp_table *t, const void *d_keys, uint64_t n,
