@@ -134,7 +134,9 @@ __global__ void __launch_bounds__(256) insert_lanes(InsertArgs A) {
       const KeyFields f = key_fields(key_hash(key, A.seed), A.log2b);
       if (!wide && try_lock(A.bk, f.p)) {
         section_begin();
-        const int r = insert_primary<TIMED>(A.bk, key, word, f, read_head(A.bk, f.p), false, A.now);
+        uint32_t expired = kUnknown;
+        const int r = insert_primary<TIMED>(A.bk, key, word, f, read_head(A.bk, f.p), false, A.now,
+                                            expired);
         if (r == kNeedPair) {
           unlock(A.bk, f.p);
         } else {

@@ -272,16 +272,23 @@ constexpr int kBusy = -2;    // a lock was taken by another lane: retry
 constexpr int kDisplaceBusy = -3;
 constexpr uint32_t kDisplaceRetries = 4;
 constexpr int kNeedPath = -1;
+constexpr uint32_t kUnknown = 0xffffffffu;  // a mask of slots that was not read
 constexpr int kNeedPair = -4;  // p's lock alone does not decide the key
 
-// Busy slots of bucket b whose entries have expired at `now`.
+// Busy slots of bucket b whose entries have expired at `now`: the value words
+// of its slots 0..3 and 4..7 are two quarters each.
 __device__ __forceinline__ uint32_t expired_mask(uint8_t *bk, uint32_t b, uint32_t busy,
                                                  uint32_t now) {
+  uint4 q[4];
+#pragma unroll
+  for (uint32_t i = 0; i < 4u; ++i) q[i] = quarter(bk, b, value_offset(2u * i));
   uint32_t m = 0u;
 #pragma unroll
-  for (uint32_t s = 0; s < kSlots; ++s)
-    if (((busy >> s) & 1u) && !word_alive(*value_ptr(bk, b, s), now)) m |= 1u << s;
-  return m;
+  for (uint32_t i = 0; i < 4u; ++i) {
+    if (!word_alive((uint64_t)q[i].x | ((uint64_t)q[i].y << 32), now)) m |= 1u << (2u * i);
+    if (!word_alive((uint64_t)q[i].z | ((uint64_t)q[i].w << 32), now)) m |= 2u << (2u * i);
+  }
+  return m & busy;
 }
 
 // Working copy of the metadata of the two buckets a key may live in (both
@@ -635,11 +642,12 @@ __device__ __forceinline__ int update_entry(uint8_t *bk, uint32_t b, uint32_t s,
 // What p's lock alone decides (see insert_direct): hp is p's head, read
 // under its lock.  Updates the key in p, or places one that is in neither
 // bucket there, and drops p's lock; or returns kNeedPair, having changed
-// nothing, with p still locked.
+// nothing, with p still locked.  expired: set to p's expired entries where it
+// looks at them.
 template <bool TIMED>
 __device__ __forceinline__ int insert_primary(uint8_t *bk, uint4 key, uint64_t word,
                                               const KeyFields &f, const Head &hp, bool plain,
-                                              uint32_t now) {
+                                              uint32_t now, uint32_t &expired) {
   const int s = find_slot(bk, f.p, hp, key, f.tag);
   if (s >= 0) {
     const int r = update_entry<TIMED>(bk, f.p, (uint32_t)s, word, now);
@@ -650,7 +658,10 @@ __device__ __forceinline__ int insert_primary(uint8_t *bk, uint4 key, uint64_t w
   if (plain || bloom_pass(hp.q1, f.bloom_bits)) return kNeedPair;
   const uint32_t meta = hp.q1.z, busy = meta_busy(meta);
   uint32_t room = ~busy & 0xffu;
-  if (TIMED && !room) room = expired_mask(bk, f.p, busy, now) & ~meta_sec(meta);
+  if (TIMED && !room) {
+    expired = expired_mask(bk, f.p, busy, now);
+    room = expired & ~meta_sec(meta);
+  }
   if (!room) return kNeedPair;
   const uint32_t fs = (uint32_t)__builtin_ctz(room), bit = 1u << fs;
   write_entry(bk, f.p, fs, key, word, f.tag, f.a);
@@ -662,12 +673,14 @@ __device__ __forceinline__ int insert_primary(uint8_t *bk, uint4 key, uint64_t w
 // The DIRECT step of an absent key under the locks of both its buckets (q1:
 // p's filter and metadata): the lowest free slot of p, else of a; with timers
 // also a slot whose entry has expired, after the free ones of its bucket;
-// else displacements.  Drops the locks.
+// else displacements.  Drops the locks.  expired_p: p's expired entries, or
+// kUnknown.
 template <bool TIMED>
 __device__ __forceinline__ int insert_pair(uint8_t *bk, uint4 key, uint64_t word,
                                            const KeyFields &f, uint64_t h, uint32_t log2b,
                                            uint64_t seed, bool plain, uint32_t now,
-                                           bool retry_displace, Pair &P, uint4 q1) {
+                                           bool retry_displace, Pair &P, uint4 q1,
+                                           uint32_t expired_p) {
   int r = kNeedPath;
   for (int xi = 0; xi < 2 && r == kNeedPath; ++xi) {
     if (xi == 1 && !plain && meta_moved(P.meta[0]) >= 0xffffu) break;
@@ -677,7 +690,9 @@ __device__ __forceinline__ int insert_pair(uint8_t *bk, uint4 key, uint64_t word
     if (busy != 0xffu) {
       fs = (uint32_t)__builtin_ctz(~busy & 0xffu);
     } else {
-      const uint32_t exp = TIMED ? expired_mask(bk, x, busy, now) : 0u;
+      const uint32_t exp = !TIMED ? 0u
+                           : xi == 0 && expired_p != kUnknown ? expired_p
+                                                              : expired_mask(bk, x, busy, now);
       if (!exp) continue;
       // prefer an entry whose removal needs no lock beyond the pair's
       uint32_t cheap = exp & ~meta_sec(P.meta[xi]);
@@ -748,7 +763,8 @@ __device__ int insert_direct(uint8_t *bk, uint4 key, uint64_t word, const KeyFie
   if (!lock_start(bk, f, pair)) return kBusy;
   const bool both = pair;  // a's lock is held too
   const Head hp = read_head(bk, f.p);
-  const int r = insert_primary<TIMED>(bk, key, word, f, hp, plain, now);
+  uint32_t expired = kUnknown;
+  const int r = insert_primary<TIMED>(bk, key, word, f, hp, plain, now, expired);
   if (r != kNeedPair) {
     if (both) unlock(bk, f.a);
     return r;
@@ -779,7 +795,7 @@ __device__ int insert_direct(uint8_t *bk, uint4 key, uint64_t word, const KeyFie
   }
   Pair P{{f.p, f.a}, {hp.q1.z, qa.z}, (uint64_t)hp.q1.x | ((uint64_t)hp.q1.y << 32)};
   return insert_pair<TIMED>(bk, key, word, f, h, log2b, seed, plain, now, retry_displace, P,
-                            hp.q1);
+                            hp.q1, expired);
 }
 
 // A cuckoo path's entries in memory (bucket | slot << 29), in groups of
