@@ -424,7 +424,9 @@ typedef struct {
  * The plan keeps the tables' device addresses, not the tables: it must be
  * destroyed before any of them, and inserts and deletes between plan
  * lookups are seen by the next one.  Host arrays are read during the call
- * only.  Starts with the launch shape {1, 128, 8, 1, CKPP_PLAN_STATIC, 8}.
+ * only.  Starts with the launch shape {1, 128, 8, 1, CKPP_PLAN_STATIC, 8};
+ * until a shape is set, lanes, block and grid are those that are fastest for
+ * the plan's lookups and tables.
  * Errors: CKPP_EINVAL (null arguments, ntables 0, overlapping ranges, bad
  * mode, tables on different devices), CKPP_ENOMEM, CKPP_EDEVICE. */
 int ckpp_plan_create(ckpp_plan **out, ckpp_table *const *tables, uint32_t ntables,

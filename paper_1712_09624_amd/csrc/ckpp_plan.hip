@@ -44,6 +44,8 @@ struct ckpp_plan {
   uint32_t nitems;
   uint32_t *d_ctr;  // next item, finished waves
   ckpp_plan_launch_t launch;
+  bool launch_set;              // a caller set `launch`
+  ckpp_plan_launch_t own;       // the shape until then (own_shape)
 };
 
 namespace {
@@ -59,6 +61,24 @@ bool valid_launch(const ckpp_plan_launch_t &L) {
          (L.block == 64 || L.block == 128 || L.block == 256) && L.blocks_per_cu >= 1 &&
          L.blocks_per_cu <= 64 && L.passes_per_item >= 1 && L.passes_per_item <= 64 &&
          (L.schedule == CKPP_PLAN_STATIC || L.schedule == CKPP_PLAN_DYNAMIC);
+}
+
+// The shape of a plan whose caller set none: that of the reported default but
+// for lanes, block and grid, so the work items are the same.  Measured on
+// MI355X, the shape taken and {1, 128, 8, 1, static, 8}: up to 2^19 lookups
+// are bound by latency more than by requests and run with one lane per lookup
+// (512 tables of 2^13..2^16 buckets, 408,000 lookups: 14.8 and 16.7 us; 1024
+// of 2^8..2^12, 265,000: 8.1 and 12.3), and so do tables that the last-level
+// cache holds for the most part (1000 of 2^12, 2M lookups: 56.6 and 60.5 us);
+// larger ones keep eight lanes (256 of 2^18 buckets, 1M lookups, 90% hits:
+// one lane 42.1, eight 39.4 us), with enough blocks for every item to start
+// when a wavefront's place is free (64 tables of 2^20 buckets, 2M lookups:
+// 84.0 and 88.6 us; 1024 of 2^10..2^18: 59.0 and 61.1).  Plans with
+// pessimistic tables gain from neither above that many lookups.
+ckpp_plan_launch_t own_shape(uint64_t lookups, uint64_t table_bytes, bool two_buffers) {
+  if (lookups <= (1u << 19) || (!two_buffers && table_bytes <= (1ull << 30)))
+    return ckpp_plan_launch_t{1u, 256u, 32u, 1u, CKPP_PLAN_STATIC, 1u};
+  return ckpp_plan_launch_t{1u, 128u, two_buffers ? 8u : 32u, 1u, CKPP_PLAN_STATIC, 8u};
 }
 
 // Cuts every batch into items of at most `tile` lookups, table by table.
@@ -109,7 +129,7 @@ int plan_lookup(ckpp_plan *p, const void *d_keys, uint8_t *d_found, uint64_t *d_
   DeviceGuard g(p->device);
   if (!g.ok()) return CKPP_EDEVICE;
   return dev_status(ckpp::launch_plan(p->d_items, p->nitems, p->d_ctr, p->two_buffers, tm,
-                                      p->launch, p->num_cus, d_keys, d_found, d_values,
+                                      p->launch_set ? p->launch : p->own, p->num_cus, d_keys, d_found, d_values,
                                       reinterpret_cast<hipStream_t>(stream)));
 }
 
@@ -127,7 +147,7 @@ int ckpp_plan_create(ckpp_plan **out, ckpp_table *const *tables, uint32_t ntable
   std::vector<PlanItem> desc(ntables);
   std::vector<uint32_t> order(ntables);
   bool two = false, any_timed = false;
-  uint64_t lookups = 0, span = 0;
+  uint64_t lookups = 0, span = 0, bytes = 0;
   for (uint32_t i = 0; i < ntables; ++i) {
     const ckpp_table *t = tables[i];
     if (!t || t->device != tables[0]->device) return CKPP_EINVAL;
@@ -142,6 +162,7 @@ int ckpp_plan_create(ckpp_plan **out, ckpp_table *const *tables, uint32_t ntable
     desc[i] = PlanItem{reinterpret_cast<const uint4 *>(t->d_table), t->seed, 0ull, 0u,
                        t->log2_buckets, mode | (tm ? ckpp::kPlanItemTimed : 0u), i};
     lookups += h_counts[i];
+    bytes += 256ull << t->log2_buckets;
     span = std::max(span, h_offsets[i] + h_counts[i]);
     order[i] = i;
   }
@@ -172,6 +193,8 @@ int ckpp_plan_create(ckpp_plan **out, ckpp_table *const *tables, uint32_t ntable
   p->d_items = nullptr;
   p->d_ctr = nullptr;
   p->nitems = 0;
+  p->launch_set = false;
+  p->own = own_shape(lookups, bytes, two);
   hipError_t e = hipMalloc(&p->d_ctr, 256);
   if (e == hipSuccess) e = hipMemset(p->d_ctr, 0, 256);
   if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -216,7 +239,9 @@ int ckpp_plan_set_launch(ckpp_plan *p, const ckpp_plan_launch_t *cfg) {
   if (!p || !cfg || !valid_launch(*cfg)) return CKPP_EINVAL;
   DeviceGuard g(p->device);
   if (!g.ok()) return CKPP_EDEVICE;
-  return build_items(p, *cfg);
+  const int rc = build_items(p, *cfg);
+  if (rc == CKPP_OK) p->launch_set = true;
+  return rc;
 }
 
 int ckpp_plan_get_launch(const ckpp_plan *p, ckpp_plan_launch_t *cfg) {
