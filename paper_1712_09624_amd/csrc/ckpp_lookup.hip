@@ -205,37 +205,39 @@ hipError_t launch_shape(const ckpp_launch_t &L, int num_cus, const TableRef &T, 
 }
 
 // The shape of a batch of n lookups in mode `mode` while no caller set one.
-// The lines measured on MI355X (n lookups, times of the shape taken and of
-// {8, 2, 128}, the shape of every larger batch):
+// The lines were measured on MI355X on keys whose buckets no cache holds from
+// an earlier batch, with 10% and 90% misses (times in us of the shape taken
+// and of {8, 2, 128}, the shape of every larger batch):
 //  - A small batch is bound by the latency of one lookup's few dependent
 //    loads, and one lane per lookup has the fewest of them between its key
-//    and its answer (65536 lookups on 2^20 buckets: 3.5 us against 7.5; 8192:
-//    2.9 against 7.4).  It stays ahead until the chip has more lookups than
-//    it can hold, since a hit reads its line twice: up to 2^18 lookups
-//    (2^20 buckets: 10.3 against 14.1 us; at 2^20 lookups 39.4 against 38.2),
-//    on tables of 4 GiB and more, whose second reads cost more, up to 2^16
-//    (2^24 buckets: 5.1 against 7.8 us; 2^17 lookups 8.1, eight lanes 6.9).
+//    and its answer (2^20 buckets, 4096 lookups: 3.6 and 8.2; 65536: 5.0 and
+//    8.8).  It stays ahead until the chip has more lookups than it can hold,
+//    since a hit reads its line twice: up to 2^18 lookups (2^22 buckets: 13.3
+//    and 15.7 with 10% misses, eight lanes 13.5; 2^19: 23.9 and 24.2, eight
+//    lanes 23.0), on tables of 4 GiB and more, whose second reads cost more,
+//    up to 2^17 (2^24 buckets: 8.7 and 12.1, eight lanes 9.3; 2^18: 14.5 and
+//    16.3, eight lanes 13.7).
 //  - In tables that stay in the L2 caches (up to 2^15 buckets, 8 MiB; 2^16
 //    for batches up to 2^21) a second read is a hit, and 32-byte heads need
 //    a quarter of the L2's bandwidth that whole lines do: one lane per lookup
 //    at every size, two lookups per lane once that fills the chip (2^20
-//    lookups on 2^14 buckets: 18.5 against 25.4 us).
+//    lookups on 2^14 buckets: 18.5 and 25.4).
 //  - In between, eight lanes with one lookup per lane in 64-thread blocks:
-//    twice the blocks of {8, 2, 128} for a last wave of blocks half as long
-//    (2^19 lookups on 2^24 buckets 21.4 against 22.9 us).  From 2^21 lookups
-//    on both take the same time on uniform keys, and two lookups per lane are
-//    6% faster on hot ones.
+//    twice the blocks of {8, 2, 128}, and the last of them half as long (2^20
+//    lookups, 2^20 buckets: 37.1 and 39.8 with 10% misses, 29.1 and 32.3 with
+//    90%).  From 2^21 lookups on both take the same time on uniform keys, and
+//    two lookups per lane are 6% faster on hot ones.
 //  - The pessimistic mode, whose lookups fetch two lines at once, needs 16
 //    KiB of LDS per wavefront with eight lanes: 64-thread blocks pack more
 //    wavefronts into a compute unit, and on tables of 1 GiB and more large
 //    batches run with four lanes, which need none (2^25 lookups on 2^24
-//    buckets 1709 against 1870 us).
+//    buckets 1709 and 1870).
 ckpp_launch_t auto_shape(const ckpp_table *t, uint64_t n, uint32_t mode) {
   const uint32_t b = t->log2_buckets;
   const bool both = mode == kModeBoth;
   const ckpp_launch_t one{1u, 1u, n <= (1u << 14) ? 64u : 256u, 0u};
   if (b <= 15u) return n <= (1u << 19) ? one : ckpp_launch_t{1u, 2u, 256u, 0u};
-  const uint32_t few = b == 16u ? 21u : b < 24u ? 18u : both ? 15u : 16u;
+  const uint32_t few = b == 16u ? 21u : b < 24u || both ? 18u : 17u;
   if (n <= (1ull << few)) return one;
   if (n <= (1u << 21)) return ckpp_launch_t{8u, 1u, 64u, 0u};
   if (both) return b >= 22u ? ckpp_launch_t{4u, 1u, 128u, 0u} : ckpp_launch_t{8u, 1u, 64u, 0u};

@@ -65,20 +65,23 @@ bool valid_launch(const ckpp_plan_launch_t &L) {
 
 // The shape of a plan whose caller set none: that of the reported default but
 // for lanes, block and grid, so the work items are the same.  Measured on
-// MI355X, the shape taken and {1, 128, 8, 1, static, 8}: up to 2^19 lookups
-// are bound by latency more than by requests and run with one lane per lookup
-// (512 tables of 2^13..2^16 buckets, 408,000 lookups: 14.8 and 16.7 us; 1024
-// of 2^8..2^12, 265,000: 8.1 and 12.3), and so do tables that the last-level
-// cache holds for the most part (1000 of 2^12, 2M lookups: 56.6 and 60.5 us);
-// larger ones keep eight lanes (256 of 2^18 buckets, 1M lookups, 90% hits:
-// one lane 42.1, eight 39.4 us), with enough blocks for every item to start
-// when a wavefront's place is free (64 tables of 2^20 buckets, 2M lookups:
-// 84.0 and 88.6 us; 1024 of 2^10..2^18: 59.0 and 61.1).  Plans with
-// pessimistic tables gain from neither above that many lookups.
+// MI355X with keys and tables that no cache holds from the last launch, the
+// shape taken and {1, 128, 8, 1, static, 8}: up to 2^18 lookups are bound by
+// latency and run with one lane per lookup (300 tables of 2^14..2^18 buckets,
+// 118,000 lookups: 7.1 and 8.7 us; 246,000: 10.9 and 12.2; 356 of 2^14,
+// 513,000: 23.1 and 21.2), and so do tables that the last-level cache holds,
+// whose second reads of a line are cheap (64 of 2^12, 4.2M lookups: 91.5 and
+// 98.8 us).  Others keep eight lanes, with enough blocks for every item to
+// start when a wavefront's place is free, of one wavefront while the last
+// blocks to end matter (those 513,000: 20.5 us; 512 tables of 2^13..2^16,
+// 408,000: 17.7 and 18.4), of two beyond (1024 of 2^10..2^18, 2.05M: 69.2 us
+// in blocks of one, 68.5 of two, and 70.5).  Plans with pessimistic tables gain
+// from neither above 2^18 lookups.
 ckpp_plan_launch_t own_shape(uint64_t lookups, uint64_t table_bytes, bool two_buffers) {
-  if (lookups <= (1u << 19) || (!two_buffers && table_bytes <= (1ull << 30)))
+  if (lookups <= (1u << 18) || (!two_buffers && table_bytes <= (256ull << 20)))
     return ckpp_plan_launch_t{1u, 256u, 32u, 1u, CKPP_PLAN_STATIC, 1u};
-  return ckpp_plan_launch_t{1u, 128u, two_buffers ? 8u : 32u, 1u, CKPP_PLAN_STATIC, 8u};
+  if (two_buffers) return ckpp_plan_launch_t{1u, 128u, 8u, 1u, CKPP_PLAN_STATIC, 8u};
+  return ckpp_plan_launch_t{1u, lookups < 2000000u ? 64u : 128u, 32u, 1u, CKPP_PLAN_STATIC, 8u};
 }
 
 // Cuts every batch into items of at most `tile` lookups, table by table.

@@ -17,7 +17,7 @@ EDGES = [
     (16, 0.9, [(1 << 21), (1 << 21) + 1]),
     (17, 0.9, [1 << 18, (1 << 18) + 1, (1 << 21) + 1]),
     (22, 0.05, [1 << 18, (1 << 18) + 1, (1 << 21) + 65]),
-    (24, 0.01, [1 << 15, (1 << 15) + 1, 1 << 16, (1 << 16) + 1]),
+    (24, 0.01, [1 << 17, (1 << 17) + 1, 1 << 18, (1 << 18) + 1]),
 ]
 
 

@@ -14,8 +14,9 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("timed", [False, True], ids=["untimed", "timed"])
 # tables, log2 buckets, lookups in all, mode
 @pytest.mark.parametrize("nt,B,total,mode", [
-    (3, 11, 1 << 19, "cuckoopp"), (3, 11, (1 << 19) + 1, "optimistic"), (3, 11, 550001, "both"),
-    (2, 22, (1 << 19) + 130, "cuckoopp"), (1, 22, 1 << 19, "both"), (2, 22, 530000, "both")])
+    (3, 11, 1 << 18, "cuckoopp"), (3, 11, (1 << 18) + 1, "optimistic"), (3, 11, 300001, "both"),
+    (2, 20, (1 << 18) + 130, "cuckoopp"), (1, 20, 1 << 18, "both"), (1, 20, 270000, "both"),
+    (1, 19, 270000, "cuckoopp"), (2, 20, 2000001, "cuckoopp")])
 def test_own_shape(nt, B, total, mode, timed):
     import torch
     from paper_1712_09624_amd.ckpp import DEFAULT_PLAN_LAUNCH, Plan, Table
