@@ -1391,8 +1391,11 @@ INSERT_WORKLOAD_HISTORY = [
     "#   317, delete 1139 M/s, re-insert 547 M/s",
     "#   two-level lookahead over every candidate at once (104 loads): 99.4 ms =",
     "#   1282.2 M/s, band 0.85: 792.5, band 0.90: 510.5, re-insert 941.6 M/s",
-    "#   one candidate at a time, walks for paths blocked by another lane's lock (previous record):",
+    "#   one candidate at a time, walks for paths blocked by another lane's lock:",
     "#   92.8 ms = 1373.9 M/s, band 0.85: 937.1, band 0.90: 633.5, re-insert 1115.6 M/s",
+    "#   blocked displacements retried; both buckets locked for every key, a path array per lane",
+    "#   (previous record): 88.8 ms = 1436.0 M/s, band 0.05: 2024, band 0.85: 1042.7, band 0.90: 751.7,",
+    "#   delete 2726 M/s, re-insert 1233.2 M/s",
 ]
 
 
@@ -1409,10 +1412,12 @@ def summarize_insert_workload(path):
            "#   slot (a path blocked by another lane's lock is retried, up to 4 times); else a random walk",
            "#   with one step of lookahead, whose path (up to 8 displacements) is applied in one critical",
            "#   section; the rare paths are compiled out of line",
-           "# path scratch: a buffer of the table's own (up to 1/32 of the table's memory, here all 2^16 lanes",
-           "#   of a batch), allocated once; the stream-ordered pool only beyond that",
+           "# path scratch: a buffer of the table's own (at most 1/8 of the table's memory), allocated once,",
+           "#   whose paths the lanes that walk take in turns",
            "# locks: table words under a lock read and written with device-coherent (agent-scope) accesses,",
-           "#   so taking and dropping a lock flushes no L2 cache",
+           "#   so taking and dropping a lock flushes no L2 cache; a key that goes into or is found in its",
+           "#   primary locks that bucket alone, reads 16 bytes at a time and unlocks with its last store",
+           "# a wavefront's keys that find no place directly go on a list and are worked off together",
            "# command (repository root): python3 bench.py --insert-workload",
            f"keys {w['keys']}  build {w['build_ms']:.1f} ms = {w['build_minserts_per_s']:.1f} M inserts/s  "
            f"failed {w['build_failed']}",
@@ -1533,7 +1538,7 @@ def summarize_serve(path, trace_dir=None, counter_dir=None):
            "# every lookup, insert status and delete result of every run checked against the ground truth",
            "# command (repository root): python3 bench.py --serve 50000",
            "# a round's updates are spread over every wavefront (lane 0 of each, then lane 1, ...); an insert",
-           "#   whose primary is full searches one- and two-step displacements with all candidates' loads at once;",
+           "#   whose buckets are full searches one- and two-step displacements, one candidate at a time;",
            "#   lookups run 4, 2 or 1 per lane per pass in registers (the loop keeps two wavefronts per SIMD);",
            "#   grid barriers: relaxed arrivals after a wait, one system-scope release per block per round",
            "# latency = host-observed completion - arrival; us/round = the loop's own clock per phase (insert:",
