@@ -16,9 +16,11 @@
 // second stage runs its state machine (insert_marked).
 //
 // Entries that are in a bucket when its block starts (the busy mask `first`)
-// keep their slots throughout, and keys of a batch are distinct, so a key is
-// compared with those entries alone and slots are claimed by a
-// compare-and-swap on the metadata word in LDS.
+// keep their slots throughout, so a key is compared with those entries, and
+// slots are claimed by a compare-and-swap on the metadata word in LDS.  A key
+// that meets its own tag in a slot taken since the start waits for the second
+// stage: a batch that breaks the rule of distinct keys leaves one entry of
+// each, as a batch taken key by key does.
 //
 // Measured on MI355X, 31.9M keys into 2^22 buckets (to load 0.95) in one call:
 // 6.9 ms key by key; this way 1.0 ms for the bins (2.3 TB/s of keys, values
@@ -151,11 +153,25 @@ __global__ void __launch_bounds__(kBulkBlock) bulk_place(BulkArgs A) {
         m = old;
       }
     }
+    if (fs != kSlots) {
+      // its tag, and then a look at the other slots taken since the start: of
+      // two copies of one key, the later to write its tag sees the other's,
+      // gives its slot back and waits for the second stage, which finds the
+      // key (so do different keys with one tag, one pair in 65,536)
+      volatile uint32_t *head = reinterpret_cast<volatile uint32_t *>(&s_head[2u * lb]);
+      reinterpret_cast<volatile uint16_t *>(head)[fs] = (uint16_t)f.tag;
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup", "local");
+      const uint4 tags = make_uint4(head[0], head[1], head[2], head[3]);
+      const uint32_t taken = meta_busy(head[6]) & ~q1.w & ~(1u << fs);
+      if (tag_eq_mask(tags, f.tag) & taken) {
+        atomicAnd(&s_head[2u * lb + 1u].z, ~(1u << (16u + fs)));
+        fs = kSlots;
+      }
+    }
     if (fs == kSlots) {
       A.status[i] = kInsertPending;
       continue;
     }
-    reinterpret_cast<uint16_t *>(&s_head[2u * lb])[fs] = (uint16_t)f.tag;
     *reinterpret_cast<uint4 *>(bucket + key_offset(fs)) = key;
     *reinterpret_cast<uint64_t *>(bucket + value_offset(fs)) = word;
     reinterpret_cast<uint32_t *>(bucket + kOtherOffset)[fs] = f.a;
@@ -244,9 +260,12 @@ hipError_t bulk_insert_primary(ckpp_table *t, const void *d_keys, const uint64_t
       (void)hipGetLastError();
       return hipSuccess;
     }
+    const hipError_t e = launch_fill_zero(p, fill_bytes, s);
+    if (e != hipSuccess) {
+      (void)hipFree(p);
+      return e;
+    }
     t->d_bulk = static_cast<uint8_t *>(p);
-    const hipError_t e = launch_fill_zero(t->d_bulk, fill_bytes, s);
-    if (e != hipSuccess) return e;
   }
   *taken = true;
   A.fill = reinterpret_cast<uint32_t *>(t->d_bulk);

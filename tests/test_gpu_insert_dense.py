@@ -132,3 +132,32 @@ def test_dense_batch_in_a_graph():
         assert bool(f.all()) and torch.equal(v, vals)
     assert int(nf.item()) == 0
     t.close()
+
+
+@pytest.mark.parametrize("apart", [1, 7, 64, 4096])
+@pytest.mark.parametrize("B,copies", [(11, 2), (13, 3)])
+def test_dense_repeated_keys(B, copies, apart):
+    """Every key `copies` times in one dense batch, its copies `apart` keys
+    from each other: one of them is INSERTED, the others are UPDATED, and the
+    table holds one entry with the value of one of them."""
+    from paper_1712_09624_amd.ckpp import Table
+    n = ((8 << B) // (2 * copies) // apart + 1) * apart
+    once = W.distinct_five_tuples(n, 500 + B)
+    at = np.repeat(np.arange(n).reshape(-1, apart), copies, axis=0).reshape(-1)
+    vals = W.insertion_values(n * copies, 3)
+    t = Table(B, W.HASH_SEED, W.MAX_KICKS, device=0)
+    say(f"dense repeated B={B} copies={copies} apart={apart} n={n * copies}")
+    st, nf = insert(t, once[at], vals)
+    st = u8(st)
+    assert int(nf.item()) == 0
+    assert np.array_equal(np.bincount(at[st == O.INSERTED], minlength=n), np.ones(n, int))
+    assert int((st == O.UPDATED).sum()) == n * (copies - 1)
+    f, v = t.lookup(to_dev(once))
+    assert u8(f).all()
+    of_key = vals[np.argsort(at, kind="stable")].reshape(n, copies)
+    assert (of_key == u64(v)[:, None]).any(axis=1).all()
+    b, k = t.export()
+    rc, msg = O.check_image(b, k, B, W.HASH_SEED)
+    assert rc == 0, f"invariant {rc}: {msg}"
+    assert t.stats()["live"] == n
+    t.close()
