@@ -19,6 +19,8 @@ using ckpp::kMaxLog2Buckets;
 constexpr uint32_t kMaxKicksLimit = 4096;
 constexpr uint32_t kMaxPathLanes = 131072;
 constexpr uint32_t kAccWords = 128;   // device accumulator words
+// ... and the bin counters of dense inserts behind them
+constexpr size_t kAccBytes = kAccWords * sizeof(uint64_t) + ckpp::kMaxBulkBins * sizeof(uint32_t);
 constexpr uint32_t kAccStats = 7 + CKPP_MOVED_BINS;
 constexpr uint32_t kAccRetry = 127;   // retry-bound counter (never cleared)
 
@@ -215,10 +217,10 @@ int ckpp_create(ckpp_table **out, uint32_t log2_buckets, uint64_t hash_seed, uin
 
   int rc = CKPP_OK;
   if (hipMalloc(&t->d_table, table_bytes(t)) != hipSuccess ||
-      hipMalloc(&t->d_stats, kAccWords * sizeof(uint64_t)) != hipSuccess) {
+      hipMalloc(&t->d_stats, kAccBytes) != hipSuccess) {
     rc = CKPP_ENOMEM;
   } else if (hipMemset(t->d_table, 0, table_bytes(t)) != hipSuccess ||
-             hipMemset(t->d_stats, 0, kAccWords * sizeof(uint64_t)) != hipSuccess ||
+             hipMemset(t->d_stats, 0, kAccBytes) != hipSuccess ||
              hipDeviceSynchronize() != hipSuccess) {
     rc = CKPP_EDEVICE;
   }
@@ -229,6 +231,7 @@ int ckpp_create(ckpp_table **out, uint32_t log2_buckets, uint64_t hash_seed, uin
     delete t;
     return rc;
   }
+  t->d_bulk_fill = reinterpret_cast<uint32_t *>(t->d_stats + kAccWords);
   *out = t;
   return CKPP_OK;
 }

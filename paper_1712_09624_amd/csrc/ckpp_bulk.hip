@@ -34,7 +34,6 @@ namespace ckpp {
 namespace {
 
 constexpr uint32_t kBulkBlock = 1024;
-constexpr uint32_t kMaxBins = 8192;         // bin counters in LDS: 32 KiB
 constexpr uint32_t kMaxBinShift = 11;       // buckets of a bin: heads in 64 KiB of LDS
 constexpr uint32_t kMinBinShift = 5;
 constexpr uint32_t kSkip = 0xffffffffu;     // a record that holds no key
@@ -59,7 +58,7 @@ struct BulkArgs {
 // writes its keys there.  Keys that find their bin full are marked.
 template <bool TIMED, uint32_t KPT>
 __global__ void __launch_bounds__(kBulkBlock) bulk_scatter(BulkArgs A) {
-  __shared__ uint32_t s_bin[kMaxBins];
+  __shared__ uint32_t s_bin[kMaxBulkBins];
   for (uint32_t b = threadIdx.x; b < A.bins; b += kBulkBlock) s_bin[b] = 0u;
   __syncthreads();
   const uint32_t i0 = blockIdx.x * (kBulkBlock * KPT) + threadIdx.x;
@@ -235,20 +234,26 @@ hipError_t bulk_insert_primary(ckpp_table *t, const void *d_keys, const uint64_t
   BulkArgs A;
   A.shift = bin_shift(log2b);
   A.bins = 1u << (log2b - A.shift);
-  // a share of the table's memory, in which the batch runs in equal chunks
+  // The bins take a share of the table's memory, in which the batch runs in
+  // equal chunks: the cuckoo-path scratch, which the second stage needs only
+  // after them, if it is as large (on tables of up to 2^15 buckets at 500
+  // kicks; with a buffer of their own the first such batch of a table of
+  // 2^13 took 78 us instead of 63, its destruction 48 instead of 32), else a
+  // buffer of their own, kept.
   uint64_t limit = (256ull << log2b) / 2u;
   if (limit > kMaxBulkBytes) limit = kMaxBulkBytes;
   if (limit < kMinBulkBytes) limit = kMinBulkBytes;
-  const uint64_t fill_bytes = (A.bins * sizeof(uint32_t) + 255u) / 256u * 256u;
+  const uint64_t path_bytes = (uint64_t)t->own_paths * path_words(t->max_kicks) * 4u;
+  const bool shared = t->d_own_paths && path_bytes >= limit;
+  if (shared) limit = path_bytes;
   uint64_t chunks = (32u * n + limit - 1u) / limit, chunk = (n + chunks - 1u) / chunks;
-  while (A.bins * bin_cap((chunk + A.bins - 1u) / A.bins) * 32u + fill_bytes > limit) {
+  while (A.bins * bin_cap((chunk + A.bins - 1u) / A.bins) * 32u > limit) {
     ++chunks;
     chunk = (n + chunks - 1u) / chunks;
   }
   A.cap = (uint32_t)bin_cap((chunk + A.bins - 1u) / A.bins);
-  if (!t->d_bulk) {
-    // the table's own buffer, kept: not under capture, and without it the
-    // batch runs the other way
+  if (!shared && !t->d_bulk) {
+    // not under capture, and without it the batch runs the other way
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &capture) != hipSuccess ||
         capture != hipStreamCaptureStatusNone) {
@@ -260,16 +265,12 @@ hipError_t bulk_insert_primary(ckpp_table *t, const void *d_keys, const uint64_t
       (void)hipGetLastError();
       return hipSuccess;
     }
-    const hipError_t e = launch_fill_zero(p, fill_bytes, s);
-    if (e != hipSuccess) {
-      (void)hipFree(p);
-      return e;
-    }
     t->d_bulk = static_cast<uint8_t *>(p);
   }
   *taken = true;
-  A.fill = reinterpret_cast<uint32_t *>(t->d_bulk);
-  A.recs = reinterpret_cast<uint4 *>(t->d_bulk + fill_bytes);
+  A.fill = t->d_bulk_fill;
+  A.recs = reinterpret_cast<uint4 *>(shared ? reinterpret_cast<uint8_t *>(t->d_own_paths)
+                                            : t->d_bulk);
   A.bk = t->d_table;
   A.log2b = log2b;
   A.seed = t->seed;
@@ -282,10 +283,9 @@ hipError_t bulk_insert_primary(ckpp_table *t, const void *d_keys, const uint64_t
     A.n = (uint32_t)(n - i < chunk ? n - i : chunk);
     const hipError_t e = timers ? launch_bulk<true>(A, s) : launch_bulk<false>(A, s);
     if (e != hipSuccess) {
-      // bins may be left filled: the next batch starts with new ones
+      // bins may be left filled: the next batch starts with empty ones
       (void)hipDeviceSynchronize();
-      (void)hipFree(t->d_bulk);
-      t->d_bulk = nullptr;
+      (void)hipMemset(t->d_bulk_fill, 0, kMaxBulkBins * sizeof(uint32_t));
       return e;
     }
   }

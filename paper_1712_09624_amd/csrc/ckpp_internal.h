@@ -18,6 +18,8 @@ struct ckpp_table {
                             // arrays), allocated on the first insert
   uint32_t own_paths;
   uint8_t *d_bulk;      // bins of dense insert batches, allocated on the first
+                        // that the path scratch is too small for
+  uint32_t *d_bulk_fill;  // records of each bin, zero between batches
   uint64_t *d_stats;    // device accumulator of ckpp_stats_t
   uint32_t retry_limit; // attempts per key on contended locks (ckpp_set_retry_limit)
   ckpp_launch_t lookup_launch;
@@ -55,11 +57,12 @@ constexpr uint8_t kInsertPending = 0xffu;
 // than fit the counters in LDS.
 constexpr uint64_t kMinBulkKeys = 4096;
 constexpr uint32_t kMaxBulkLog2Buckets = 24;
+constexpr uint32_t kMaxBulkBins = 8192;  // their counters in LDS: 32 KiB
 inline uint64_t min_bulk_keys(uint32_t log2b) {
   const uint64_t n = (log2b < 24u ? 2ull : 3ull) << log2b;
   return n < kMinBulkKeys ? kMinBulkKeys : n;
 }
-// The bins' buffer: half of the table's memory within these bounds.
+// The bins' memory: half of the table's own within these bounds.
 constexpr uint64_t kMinBulkBytes = 4ull << 20;
 constexpr uint64_t kMaxBulkBytes = 512ull << 20;
 
