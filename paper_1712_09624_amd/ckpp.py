@@ -285,8 +285,9 @@ def _zero_word(device, stream: int):
         except IndexError:
             with torch.inference_mode(False):  # ordinary tensors, whoever asks first
                 block = torch.zeros(_ZERO_WORDS, dtype=torch.int64, device=device)
-                words.extend(block.split(1))
-            return words.pop()
+                word, *rest = block.split(1)
+            words.extend(rest)
+            return word  # not popped: another thread may have taken them all
     return torch.zeros(1, dtype=torch.int64, device=device)
 
 
