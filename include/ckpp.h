@@ -151,8 +151,8 @@ int ckpp_clear(ckpp_table *t, void *stream);
  * at once take turns.  (A first insert on a stream under capture takes it
  * from the device's stream-ordered memory pool.)  A dense batch, two keys per
  * bucket or more, is binned by bucket first, in the path scratch or, if that
- * is too small, a second buffer of the table's own: half of the table's
- * device memory, between 4 and 512 MiB, allocated on the first such batch and
+ * is too small, a second buffer of the table's own: 5/8 of the table's
+ * device memory, at least 4 MiB, allocated on the first such batch and
  * freed with the table (without it, on a stream under capture or out of
  * memory, the batch runs key by key, with the same results).  Two insert batches of one table must therefore not
  * overlap in time (order them on one stream).

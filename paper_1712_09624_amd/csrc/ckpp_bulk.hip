@@ -23,8 +23,8 @@
 // each, as a batch taken key by key does.
 //
 // Measured on MI355X, 31.9M keys into 2^22 buckets (to load 0.95) in one call:
-// 6.9 ms key by key; this way 1.0 ms for the bins (2.3 TB/s of keys, values
-// and records), 1.6 ms for their blocks, 2.3 ms for the 4M keys of the second
+// 6.9 ms key by key; this way 1.1 ms for the bins (2.0 TB/s of keys, values
+// and records), 1.2 ms for their blocks, 2.1 ms for the 4M keys of the second
 // stage.
 
 #include "ckpp_device.h"
@@ -34,7 +34,7 @@ namespace ckpp {
 namespace {
 
 constexpr uint32_t kBulkBlock = 1024;
-constexpr uint32_t kMaxBinShift = 11;       // buckets of a bin: heads in 64 KiB of LDS
+constexpr uint32_t kMaxBinShift = 8;        // buckets of a bin, unless the bins get too many
 constexpr uint32_t kMinBinShift = 5;
 constexpr uint32_t kSkip = 0xffffffffu;     // a record that holds no key
 
@@ -205,11 +205,17 @@ hipError_t launch_bulk(const BulkArgs &A, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Buckets per bin: enough bins for two blocks on every compute unit, heads
-// within 64 KiB.
+// Buckets per bin: enough bins for two blocks on every compute unit, and at
+// most 2^8 buckets, 64 KiB of the table per block, so that the three stores
+// of a key meet in the L2 cache before its lines leave it (2^11 per bin,
+// 512 KiB, and 2^8: 8M keys into 2^20 buckets 1.49 and 1.36 ms, half of them
+// 447 and 356 us; 31.9M into 2^22 5.09 and 4.62), but no more than
+// kMaxBulkBins bins (2^24 buckets at load 0.9 in 8192 and in 16384 bins: 18.2
+// and 17.5 ms).
 uint32_t bin_shift(uint32_t log2b) {
-  const uint32_t s = log2b > 9u ? log2b - 9u : 0u;
-  return s < kMinBinShift ? kMinBinShift : s > kMaxBinShift ? kMaxBinShift : s;
+  const uint32_t few = log2b > 9u ? log2b - 9u : 0u;
+  const uint32_t s = few < kMinBinShift ? kMinBinShift : few > kMaxBinShift ? kMaxBinShift : few;
+  return log2b > s + kMaxBulkLog2Bins ? log2b - kMaxBulkLog2Bins : s;
 }
 
 // Records of a bin for `mean` keys: a bin's count is close to Poisson, and
@@ -240,8 +246,7 @@ hipError_t bulk_insert_primary(ckpp_table *t, const void *d_keys, const uint64_t
   // kicks; with a buffer of their own the first such batch of a table of
   // 2^13 took 78 us instead of 63, its destruction 48 instead of 32), else a
   // buffer of their own, kept.
-  uint64_t limit = (256ull << log2b) / 2u;
-  if (limit > kMaxBulkBytes) limit = kMaxBulkBytes;
+  uint64_t limit = (256ull << log2b) / 8u * 5u;
   if (limit < kMinBulkBytes) limit = kMinBulkBytes;
   const uint64_t path_bytes = (uint64_t)t->own_paths * path_words(t->max_kicks) * 4u;
   const bool shared = t->d_own_paths && path_bytes >= limit;

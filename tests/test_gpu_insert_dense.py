@@ -161,3 +161,29 @@ def test_dense_repeated_keys(B, copies, apart):
     assert rc == 0, f"invariant {rc}: {msg}"
     assert t.stats()["live"] == n
     t.close()
+
+
+@pytest.mark.parametrize("B,n", [(22, 2 << 22), (23, (2 << 23) + 1), (24, (3 << 24) + 5)])
+def test_dense_large_tables(B, n):
+    """The largest bin counts (2^14 bins of 2^8, 2^9 and 2^10 buckets), in the
+    fewest keys that are taken this way; keys drawn on the device."""
+    import torch
+
+    from paper_1712_09624_amd.ckpp import Table
+    g = torch.Generator(device="cuda").manual_seed(B)
+    keys = torch.randint(-(1 << 63), (1 << 63) - 1, (n, 2), dtype=torch.int64, device="cuda",
+                         generator=g).view(torch.uint8)
+    vals = torch.arange(n, dtype=torch.int64, device="cuda") * 3 + 1
+    t = Table(B, W.HASH_SEED, W.MAX_KICKS, device=0)
+    say(f"dense large B={B} n={n}")
+    st, nf = t.insert(keys, vals)
+    assert int(nf.item()) == 0 and not bool(st.any())
+    s = t.stats()
+    assert s["live"] == n and s["locked"] == 0 and s["retry_exhausted"] == 0
+    f, v = t.lookup(keys)
+    assert bool(f.all()) and torch.equal(v, vals)
+    gone = t.delete(keys)
+    assert bool(gone.all())
+    s = t.stats()
+    assert s["live"] == 0 and s["bloom_pc_sum"] == 0
+    t.close()
