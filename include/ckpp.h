@@ -150,7 +150,7 @@ int ckpp_clear(ckpp_table *t, void *stream);
  * device memory, but at least 4096; keys that search a path beyond that many
  * at once take turns.  (A first insert on a stream under capture takes it
  * from the device's stream-ordered memory pool.)  A dense batch, two keys per
- * bucket or more, is binned by bucket first, in the path scratch or, if that
+ * bucket or more (one on 2^20 buckets and more), is binned by bucket first, in the path scratch or, if that
  * is too small, a second buffer of the table's own: 5/8 of the table's
  * device memory, at least 4 MiB, allocated on the first such batch and
  * freed with the table (without it, on a stream under capture or out of

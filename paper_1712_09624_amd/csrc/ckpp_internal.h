@@ -47,20 +47,20 @@ constexpr uint64_t kOwnPathShare = 8;
 // Dense insert batches (ckpp_bulk.hip).  Status of a key that waits for the
 // second stage.
 constexpr uint8_t kInsertPending = 0xffu;
-// The batches that take that way hold at least kMinBulkKeys keys and two per
-// bucket of the table.  Measured on MI355X, one key per bucket, this way and
-// the other: 2^18 buckets 32 and 38 us from empty, 53 and 53 us from load
-// 0.5; 2^20 buckets 103 and 103, 143 and 132; 2^22 buckets 518 and 643, 665
-// and 771.  Tables of 2^24 buckets have so many bins that a block writes only
-// two records to each: three keys per bucket (one: 2829 and 2523 us, 3248 and
-// 2926; four, from load 0.5: 15.2 and 18.6 ms).  Larger tables have more bins
-// than fit the counters in LDS.
+// The batches that take that way hold at least kMinBulkKeys keys and, per
+// bucket of the table, one on 2^20 buckets and more, two on fewer.  Measured
+// on MI355X, this way and the other, from empty and from load 0.5, in us:
+// one key per bucket, 2^18 buckets 36 and 39, 61 and 57; 2^20 buckets 132 and
+// 205, 194 and 232; 2^22 buckets 548 and 664, 698 and 791; 2^24 buckets 2093
+// and 2562, 2580 and 2945; half a key, 2^22 buckets 383 and 338, 431 and 391.
+// One and a half, 2^16 buckets 21 and 27, 54 and 45.  Larger tables have more
+// bins than fit the counters in LDS.
 constexpr uint64_t kMinBulkKeys = 4096;
 constexpr uint32_t kMaxBulkLog2Buckets = 24;
 constexpr uint32_t kMaxBulkLog2Bins = 14;  // their counters in LDS: 64 KiB
 constexpr uint32_t kMaxBulkBins = 1u << kMaxBulkLog2Bins;
 inline uint64_t min_bulk_keys(uint32_t log2b) {
-  const uint64_t n = (log2b < 24u ? 2ull : 3ull) << log2b;
+  const uint64_t n = (log2b < 20u ? 2ull : 1ull) << log2b;
   return n < kMinBulkKeys ? kMinBulkKeys : n;
 }
 // The bins' memory: 5/8 of the table's own, in which a full table's keys fit

@@ -163,10 +163,13 @@ def test_dense_repeated_keys(B, copies, apart):
     t.close()
 
 
-@pytest.mark.parametrize("B,n", [(22, 2 << 22), (23, (2 << 23) + 1), (24, (3 << 24) + 5)])
+@pytest.mark.parametrize("B,n", [(19, (2 << 19) - 1), (19, 2 << 19), (20, (1 << 20) - 1),
+                                 (20, 1 << 20), (22, 2 << 22), (23, (1 << 23) + 1),
+                                 (24, 1 << 24), (24, (3 << 24) + 5)])
 def test_dense_large_tables(B, n):
-    """The largest bin counts (2^14 bins of 2^8, 2^9 and 2^10 buckets), in the
-    fewest keys that are taken this way; keys drawn on the device."""
+    """The least keys per bucket on each side of 2^20 buckets, and the largest
+    bin counts (2^14 bins of 2^8, 2^9 and 2^10 buckets); keys drawn on the
+    device."""
     import torch
 
     from paper_1712_09624_amd.ckpp import Table
