@@ -1161,7 +1161,10 @@ __device__ InsertOutcome insert_one(uint8_t *bk, uint4 key, uint64_t value, uint
 // an expired entry of the key is removed too, but reports 0 (Sec. 4.2).  As
 // in insert_direct, p's lock alone decides a key that is in p or fails p's
 // filter.  Removing from p writes p's metadata word alone, with the unlock,
-// so nothing is waited for.
+// and on a table without timers nothing is left to wait for: what the section
+// read has decided that word.  The time of an expired entry decides only the
+// answer, so with timers the unlock waits for it (the next holder of the lock
+// may write another entry's time there).
 template <bool TIMED>
 __device__ int delete_direct(uint8_t *bk, uint4 key, const KeyFields &f, bool plain,
                              uint32_t now, bool &pair) {
@@ -1177,6 +1180,7 @@ __device__ int delete_direct(uint8_t *bk, uint4 key, const KeyFields &f, bool pl
       const uint32_t bit = 1u << s;
       r = (!TIMED || word_alive(value_ptr(bk, f.p, (uint32_t)s)[0], now)) ? 1 : 0;
       m = make_meta(meta_moved(mp), meta_busy(mp) & ~bit, meta_sec(mp) & ~bit);
+      if (TIMED) section_end();
     }
     unlock_meta(bk, f.p, m);
     if (both) unlock(bk, f.a);
