@@ -248,15 +248,17 @@ def _torch():
     return _torch_module
 
 
-def _current_stream_handle() -> int:
-    """Handle of the current device's current stream.  torch.cuda.current_stream()
-    builds a Stream object each time (2.7 us, of a small lookup call's 7.5 on
-    an MI355X host); torch hands out the bare handle in 0.1 us."""
+def _current_stream_handle(device=None) -> int:
+    """Handle of a device's (the current one's) current stream.
+    torch.cuda.current_stream() builds a Stream object each time (2.7 us, of a
+    small lookup call's 7.5 on an MI355X host); torch hands out the bare handle
+    in 0.1 us."""
     torch = _torch()
+    index = torch.cuda.current_device() if device is None else device.index
     raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
     if raw is None:
-        return int(torch.cuda.current_stream().cuda_stream)
-    return int(raw(torch.cuda.current_device()))
+        return int(torch.cuda.current_stream(index).cuda_stream)
+    return int(raw(index))
 
 
 def _stream_handle(stream) -> int:
@@ -275,10 +277,13 @@ def _zero_word(device, stream: int):
     made its own counter spent 5 us of host time, and the device one more
     launch, on clearing 8 bytes; on a device's null stream the word comes from
     a block of them cleared together, each handed out once.  The null stream
-    is never destroyed and never captured, so the clearing always comes
-    before the insert; on every other stream the word is cleared by itself."""
+    is never destroyed and never captured, so a block that is cleared there is
+    cleared before any call on it counts.  torch clears on the device's current
+    stream, which need not be the call's: a word is taken from a block only
+    where both are the null stream, and is cleared by itself everywhere
+    else."""
     torch = _torch()
-    if stream == 0 and torch.cuda.current_device() == device.index:
+    if stream == 0 and _current_stream_handle(device) == 0:
         words = _zero_words.setdefault(device.index, [])
         try:
             return words.pop()

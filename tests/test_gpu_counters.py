@@ -71,3 +71,26 @@ def test_scan_counters():
     torch.cuda.synchronize()
     assert [int(x.item()) for x in gone] == [200, 0, 200, 200]
     t.close()
+
+
+def test_null_stream_call_while_a_side_stream_is_current():
+    """A call that names the null stream while a busy side stream is current
+    leaves nothing behind that later calls on the null stream count in."""
+    import torch
+    from paper_1712_09624_amd.ckpp import Table
+    keys, vals = to_dev(W.distinct_five_tuples(20, 5)), vals_dev(W.insertion_values(20))
+    st = torch.empty(20, dtype=torch.uint8, device="cuda:0")
+    t = Table(1, W.HASH_SEED, W.MAX_KICKS, device=0)
+    t.insert(keys, vals)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    say("inserts that name the null stream while a side stream is current")
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(20_000_000)
+        first = [t.insert(keys, vals, status=st, stream=s)[1]
+                 for s in (0, torch.cuda.default_stream())]
+    got = [t.insert(keys, vals)[1] for _ in range(20)]
+    torch.cuda.synchronize()
+    assert [int(x.item()) for x in got] == [4] * 20
+    assert len(first) == 2
+    t.close()
