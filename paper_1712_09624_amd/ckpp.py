@@ -290,8 +290,10 @@ def _zero_word(device, stream: int):
         except IndexError:
             with torch.inference_mode(False):  # ordinary tensors, whoever asks first
                 block = torch.zeros(_ZERO_WORDS, dtype=torch.int64, device=device)
-                word, *rest = block.split(1)
-            words.extend(rest)
+                # .data: a version counter of each word's own
+                word, *rest = [w.data for w in block.split(1)]
+            if type(block) is torch.Tensor:  # no stand-in of a tracing mode is kept
+                words.extend(rest)
             return word  # not popped: another thread may have taken them all
     return torch.zeros(1, dtype=torch.int64, device=device)
 

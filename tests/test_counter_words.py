@@ -11,7 +11,7 @@ from paper_1712_09624_amd import ckpp
 
 class Word:
     def __init__(self, n, stream):
-        self.n, self.stream = n, stream
+        self.n, self.stream, self.data = n, stream, self
 
     def split(self, k):
         return tuple(Word(k, self.stream) for _ in range(self.n // k))
@@ -20,7 +20,7 @@ class Word:
 @pytest.fixture
 def fake(monkeypatch):
     """torch with the current stream `handle` on every device."""
-    t = types.SimpleNamespace(handle=0, int64=None)
+    t = types.SimpleNamespace(handle=0, int64=None, Tensor=Word)
     t.cuda = types.SimpleNamespace(current_device=lambda: 0)
     t._C = types.SimpleNamespace(_cuda_getCurrentRawStream=lambda device: t.handle)
     t.inference_mode = lambda on: contextlib.nullcontext()
@@ -50,3 +50,20 @@ def test_no_block_on_another_stream(fake, current, call):
     assert not any(ckpp._zero_words.values())
     fake.handle = 0
     assert ckpp._zero_word(DEVICE, 0).stream == 0
+
+
+def test_words_are_plain_tensors_of_their_own(monkeypatch):
+    """A block made under a tracing mode that hands out stand-ins is not kept
+    for later calls, and writing to one word does not look like writing to
+    another (autograd's version counter)."""
+    import torch
+    from torch._subclasses.fake_tensor import FakeTensor, FakeTensorMode
+    monkeypatch.setattr(ckpp, "_zero_words", {})
+    monkeypatch.setattr(ckpp, "_current_stream_handle", lambda device=None: 0)
+    cpu = torch.device("cpu")
+    with FakeTensorMode():
+        assert isinstance(ckpp._zero_word(cpu, 0), FakeTensor)
+    a, b = ckpp._zero_word(cpu, 0), ckpp._zero_word(cpu, 0)
+    assert type(a) is type(b) is torch.Tensor and a.shape == b.shape == (1,)
+    a.add_(5)
+    assert (a.item(), b.item(), b._version) == (5, 0, 0)
