@@ -134,6 +134,44 @@ def test_dense_batch_in_a_graph():
     t.close()
 
 
+@pytest.mark.parametrize("timed", [False, True], ids=["untimed", "timed"])
+@pytest.mark.parametrize("B,top", [(11, False), (11, True), (16, True)],
+                         ids=["B11_first_bins", "B11_last_bins", "B16_last_bins"])
+def test_dense_full_bins(B, top, timed):
+    """All primaries in one eighth of the buckets, the first or the last: eight
+    times a bin's mean, so that most keys find their bin full.  Then a uniform
+    batch with half of those keys again, whose bins start empty."""
+    from paper_1712_09624_amd.ckpp import Table
+    nb, n = 1 << B, 2 << B
+    drawn = W.distinct_five_tuples(9 * n, 460 + B)
+    p = O.hash_keys(drawn, W.HASH_SEED) & np.uint64(nb - 1)
+    here = (p >= nb - nb // 8) if top else (p < nb // 8)
+    keys, fresh = drawn[here][:n], drawn[~here][:n]
+    assert len(keys) == len(fresh) == n
+    vals = W.insertion_values(2 * n, 5)
+    exp = np.full(2 * n, 700, np.uint16) if timed else None
+    t = Table(B, W.HASH_SEED, W.MAX_KICKS, device=0, timers=timed)
+    say(f"dense full bins B={B} n={n} top={top} timed={timed}")
+    st, nf = insert(t, keys, vals[:n], None if exp is None else exp[:n])
+    assert not u8(st).any() and int(nf.item()) == 0
+    both = np.concatenate([keys, fresh])
+    rows = np.r_[W.choose_rows(n, n // 2, 8), np.arange(n, 2 * n)]
+    rows = rows[np.argsort(W.raw_u64(12, 0, len(rows)))]
+    vals[rows] += np.uint64(10**9)
+    say(f"dense uniform B={B} n={len(rows)}")
+    st, nf = insert(t, both[rows], vals[rows], None if exp is None else exp[rows])
+    assert int(nf.item()) == 0
+    assert np.array_equal(u8(st), np.where(rows < n, O.UPDATED, O.INSERTED).astype(np.uint8))
+    f, v = t.lookup_at(to_dev(both), 100) if timed else t.lookup(to_dev(both))
+    assert u8(f).all() and np.array_equal(u64(v), vals)
+    b, k = t.export()
+    rc, msg = O.check_image(b, k, B, W.HASH_SEED, timed=timed)
+    assert rc == 0, f"invariant {rc}: {msg}"
+    s = t.stats()
+    assert s["live"] == 2 * n and s["locked"] == 0 and s["retry_exhausted"] == 0
+    t.close()
+
+
 @pytest.mark.parametrize("apart", [1, 7, 64, 4096])
 @pytest.mark.parametrize("B,copies", [(11, 2), (13, 3)])
 def test_dense_repeated_keys(B, copies, apart):
