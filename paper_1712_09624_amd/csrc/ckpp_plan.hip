@@ -72,16 +72,19 @@ bool valid_launch(const ckpp_plan_launch_t &L) {
 // 513,000: 23.1 and 21.2), and so do tables that the last-level cache holds,
 // whose second reads of a line are cheap (64 of 2^12, 4.2M lookups: 91.5 and
 // 98.8 us).  Others keep eight lanes, with enough blocks for every item to
-// start when a wavefront's place is free, of one wavefront while the last
-// blocks to end matter (those 513,000: 20.5 us; 512 tables of 2^13..2^16,
-// 408,000: 17.7 and 18.4), of two beyond (1024 of 2^10..2^18, 2.05M: 69.2 us
-// in blocks of one, 68.5 of two, and 70.5).  Plans with pessimistic tables gain
+// start when a wavefront's place is free.  Below 2^20 lookups, where the last
+// blocks to end are a larger part, blocks of one wavefront, beyond of two (us
+// in blocks of one, of two, and {1, 128, 8, 1, static, 8}; fleets of tables
+// of 2^10..2^18 buckets): 288,000 lookups 13.2, 13.1 and 14.8; 545,000 20.4,
+// 21.3 and 22.0; 586,000 23.8, 24.5 and 25.2; 1.10M 38.9, 38.5 and 39.4; 1.75M
+// 61.0, 59.1 and 61.9; 2.05M 70.7, 69.8 and 70.7; 4.09M 125.6, 122.3 and 124.9;
+// 8.16M 223, 218 and 221.  Plans with pessimistic tables gain
 // from neither above 2^18 lookups.
 ckpp_plan_launch_t own_shape(uint64_t lookups, uint64_t table_bytes, bool two_buffers) {
   if (lookups <= (1u << 18) || (!two_buffers && table_bytes <= (256ull << 20)))
     return ckpp_plan_launch_t{1u, 256u, 32u, 1u, CKPP_PLAN_STATIC, 1u};
   if (two_buffers) return ckpp_plan_launch_t{1u, 128u, 8u, 1u, CKPP_PLAN_STATIC, 8u};
-  return ckpp_plan_launch_t{1u, lookups < 2000000u ? 64u : 128u, 32u, 1u, CKPP_PLAN_STATIC, 8u};
+  return ckpp_plan_launch_t{1u, lookups < (1u << 20) ? 64u : 128u, 32u, 1u, CKPP_PLAN_STATIC, 8u};
 }
 
 // Cuts every batch into items of at most `tile` lookups, table by table.
@@ -132,8 +135,8 @@ int plan_lookup(ckpp_plan *p, const void *d_keys, uint8_t *d_found, uint64_t *d_
   DeviceGuard g(p->device);
   if (!g.ok()) return CKPP_EDEVICE;
   return dev_status(ckpp::launch_plan(p->d_items, p->nitems, p->d_ctr, p->two_buffers, tm,
-                                      p->launch_set ? p->launch : p->own, p->num_cus, d_keys, d_found, d_values,
-                                      reinterpret_cast<hipStream_t>(stream)));
+                                      p->launch_set ? p->launch : p->own, p->num_cus, d_keys,
+                                      d_found, d_values, reinterpret_cast<hipStream_t>(stream)));
 }
 
 
