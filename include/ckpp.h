@@ -353,7 +353,10 @@ int ckpp_info(const ckpp_table *t, ckpp_info_t *out);
  * {8, 2, 128, 0}, the fastest shape for large batches on 2^17..2^24-bucket
  * tables; until a shape is set, other batches run in the shape that is
  * fastest for their size, mode and table size: the smallest as {1, 1, 64,
- * 0}, which completes them soonest.  Errors: CKPP_EINVAL (a shape outside these sets). */
+ * 0}, which completes them soonest.  ckpp_get_lookup_launch reports the shape
+ * that was set, or the one a table starts with; setting the latter pins it
+ * for every batch, and ckpp_reset_lookup_launch makes the table as it started
+ * again.  Errors: CKPP_EINVAL (a shape outside these sets, null arguments). */
 typedef struct {
     uint32_t lanes_per_lookup;
     uint32_t lookups_per_lane;
@@ -363,6 +366,7 @@ typedef struct {
 
 int ckpp_set_lookup_launch(ckpp_table *t, const ckpp_launch_t *cfg);
 int ckpp_get_lookup_launch(const ckpp_table *t, ckpp_launch_t *cfg);
+int ckpp_reset_lookup_launch(ckpp_table *t);
 
 /* Retry limit of inserts and deletes (this library's bound; the paper's
  * table has one writer per core, Sec. 2, and never meets a held lock): the
@@ -463,9 +467,15 @@ int ckpp_plan_lookup_at(ckpp_plan *p, const void *d_keys, uint8_t *d_found, uint
  * not for use under graph capture).  The work items move to new device
  * memory, so a HIP graph captured from an earlier ckpp_plan_lookup of this
  * plan must not be launched afterwards (capture it again).
- * Errors: CKPP_EINVAL (out of range). */
+ * ckpp_plan_get_launch reports the shape that was set, or the one a plan
+ * starts with, whatever lanes, block and grid the plan then runs with; setting
+ * the latter pins it, and ckpp_plan_reset_launch (which rebuilds the work items
+ * too) makes the plan as it started again.
+ * Errors: CKPP_EINVAL (out of range, null arguments), CKPP_ENOMEM,
+ * CKPP_EDEVICE. */
 int ckpp_plan_set_launch(ckpp_plan *p, const ckpp_plan_launch_t *cfg);
 int ckpp_plan_get_launch(const ckpp_plan *p, ckpp_plan_launch_t *cfg);
+int ckpp_plan_reset_launch(ckpp_plan *p);
 int ckpp_plan_info(const ckpp_plan *p, ckpp_plan_info_t *out);
 
 /* ---- Serving: a device-resident request loop --------------------------

@@ -184,6 +184,7 @@ SIGNATURES = [
     ("ckpp_info", _I, [_VP, ctypes.POINTER(_Info)]),
     ("ckpp_set_lookup_launch", _I, [_VP, ctypes.POINTER(_Launch)]),
     ("ckpp_get_lookup_launch", _I, [_VP, ctypes.POINTER(_Launch)]),
+    ("ckpp_reset_lookup_launch", _I, [_VP]),
     ("ckpp_set_retry_limit", _I, [_VP, _U32]),
     ("ckpp_get_retry_limit", _I, [_VP, ctypes.POINTER(_U32)]),
     ("ckpp_check_image", _I, [_U32, _U32, _VP, _VP]),
@@ -194,6 +195,7 @@ SIGNATURES = [
                                  _VP]),
     ("ckpp_plan_set_launch", _I, [_VP, ctypes.POINTER(_PlanLaunch)]),
     ("ckpp_plan_get_launch", _I, [_VP, ctypes.POINTER(_PlanLaunch)]),
+    ("ckpp_plan_reset_launch", _I, [_VP]),
     ("ckpp_plan_info", _I, [_VP, ctypes.POINTER(_PlanInfo)]),
     ("ckpp_server_create", _I, [ctypes.POINTER(_VP), _VP, ctypes.POINTER(_ServerConfig)]),
     ("ckpp_server_rings", _I, [_VP, ctypes.POINTER(_ServerRings)]),
@@ -331,6 +333,8 @@ def check_image(log2_buckets: int, buckets: np.ndarray, kv: np.ndarray, plain: b
 
 class Table:
     """A Cuckoo++ hash table in device memory (see include/ckpp.h)."""
+
+    launch_set = False  # set_lookup_launch was called (and not reset since)
 
     def __init__(self, log2_buckets: int, hash_seed: int = DEFAULT_HASH_SEED,
                  max_kicks: int = 500, plain: bool = False, device: int | None = None,
@@ -567,6 +571,12 @@ class Table:
         cfg = _Launch(lanes_per_lookup, lookups_per_lane, block, blocks_per_cu)
         _check(self.lib.ckpp_set_lookup_launch(self._h, ctypes.byref(cfg)),
                "ckpp_set_lookup_launch")
+        self.launch_set = True
+
+    def reset_lookup_launch(self):
+        """No set shape again: each batch takes the one fastest for its size."""
+        _check(self.lib.ckpp_reset_lookup_launch(self._h), "ckpp_reset_lookup_launch")
+        self.launch_set = False
 
     def get_lookup_launch(self) -> dict:
         cfg = _Launch()
@@ -580,6 +590,8 @@ class Plan:
     ckpp_plan_create in include/ckpp.h).  ``offsets[i]``/``counts[i]`` place
     table i's batch in the concatenated key array; ``modes`` (names or
     numbers, default Cuckoo++) gives each table's lookup mode."""
+
+    launch_set = False  # set_launch was called (and not reset since)
 
     def __init__(self, tables, offsets, counts, modes=None):
         self.lib = load()
@@ -658,6 +670,12 @@ class Plan:
         cfg = _PlanLaunch(lookups_per_lane, block, blocks_per_cu, passes_per_item, schedule,
                           lanes_per_lookup)
         _check(self.lib.ckpp_plan_set_launch(self._h, ctypes.byref(cfg)), "ckpp_plan_set_launch")
+        self.launch_set = True
+
+    def reset_launch(self):
+        """No set shape again: the plan runs in its own."""
+        _check(self.lib.ckpp_plan_reset_launch(self._h), "ckpp_plan_reset_launch")
+        self.launch_set = False
 
     def get_launch(self) -> dict:
         cfg = _PlanLaunch()

@@ -18,6 +18,7 @@ using ckpp::dev_status;
 using ckpp::kMaxLog2Buckets;
 constexpr uint32_t kMaxKicksLimit = 4096;
 constexpr uint32_t kMaxPathLanes = 131072;
+constexpr ckpp_launch_t kStartLaunch = {8, 2, 128, 0};
 constexpr uint32_t kAccWords = 128;   // device accumulator words
 // ... and the bin counters of dense inserts behind them
 constexpr size_t kAccBytes = kAccWords * sizeof(uint64_t) + ckpp::kMaxBulkBins * sizeof(uint32_t);
@@ -189,10 +190,7 @@ int ckpp_create(ckpp_table **out, uint32_t log2_buckets, uint64_t hash_seed, uin
   t->device = device;
   t->seed = hash_seed;
   t->retry_limit = ckpp::kMaxRetryLimit;
-  t->lookup_launch.lanes_per_lookup = 8;
-  t->lookup_launch.lookups_per_lane = 2;
-  t->lookup_launch.block = 128;
-  t->lookup_launch.blocks_per_cu = 0;
+  t->lookup_launch = kStartLaunch;
   hipDeviceProp_t prop;
   if (hipGetDeviceProperties(&prop, device) != hipSuccess) {
     delete t;
@@ -471,6 +469,13 @@ int ckpp_set_lookup_launch(ckpp_table *t, const ckpp_launch_t *cfg) {
 int ckpp_get_lookup_launch(const ckpp_table *t, ckpp_launch_t *cfg) {
   if (!t || !cfg) return CKPP_EINVAL;
   *cfg = t->lookup_launch;
+  return CKPP_OK;
+}
+
+int ckpp_reset_lookup_launch(ckpp_table *t) {
+  if (!t) return CKPP_EINVAL;
+  t->lookup_launch = kStartLaunch;
+  t->launch_set = false;
   return CKPP_OK;
 }
 

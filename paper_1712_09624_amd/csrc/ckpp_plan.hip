@@ -63,6 +63,9 @@ bool valid_launch(const ckpp_plan_launch_t &L) {
          (L.schedule == CKPP_PLAN_STATIC || L.schedule == CKPP_PLAN_DYNAMIC);
 }
 
+// The shape a plan reports until its caller sets one.
+constexpr ckpp_plan_launch_t kStartLaunch = {1u, 128u, 8u, 1u, CKPP_PLAN_STATIC, 8u};
+
 // The shape of a plan whose caller set none: that of the reported default but
 // for lanes, block and grid, so the work items are the same.  Measured on
 // MI355X with keys and tables that no cache holds from the last launch, the
@@ -83,7 +86,7 @@ bool valid_launch(const ckpp_plan_launch_t &L) {
 ckpp_plan_launch_t own_shape(uint64_t lookups, uint64_t table_bytes, bool two_buffers) {
   if (lookups <= (1u << 18) || (!two_buffers && table_bytes <= (256ull << 20)))
     return ckpp_plan_launch_t{1u, 256u, 32u, 1u, CKPP_PLAN_STATIC, 1u};
-  if (two_buffers) return ckpp_plan_launch_t{1u, 128u, 8u, 1u, CKPP_PLAN_STATIC, 8u};
+  if (two_buffers) return kStartLaunch;
   return ckpp_plan_launch_t{1u, lookups < (1u << 20) ? 64u : 128u, 32u, 1u, CKPP_PLAN_STATIC, 8u};
 }
 
@@ -208,8 +211,7 @@ int ckpp_plan_create(ckpp_plan **out, ckpp_table *const *tables, uint32_t ntable
     free_plan(p);
     return dev_status(e);
   }
-  const ckpp_plan_launch_t L{1u, 128u, 8u, 1u, CKPP_PLAN_STATIC, 8u};
-  const int rc = build_items(p, L);
+  const int rc = build_items(p, kStartLaunch);
   if (rc != CKPP_OK) {
     free_plan(p);
     return rc;
@@ -247,6 +249,15 @@ int ckpp_plan_set_launch(ckpp_plan *p, const ckpp_plan_launch_t *cfg) {
   if (!g.ok()) return CKPP_EDEVICE;
   const int rc = build_items(p, *cfg);
   if (rc == CKPP_OK) p->launch_set = true;
+  return rc;
+}
+
+int ckpp_plan_reset_launch(ckpp_plan *p) {
+  if (!p) return CKPP_EINVAL;
+  DeviceGuard g(p->device);
+  if (!g.ok()) return CKPP_EDEVICE;
+  const int rc = build_items(p, kStartLaunch);
+  if (rc == CKPP_OK) p->launch_set = false;
   return rc;
 }
 
