@@ -146,13 +146,16 @@ int ckpp_clear(ckpp_table *t, void *stream);
  * FAILED keys (RETRY keys are counted in ckpp_stats_t.retry_exhausted).
  * The cuckoo-path scratch of the call is a buffer of the table's own,
  * allocated on its first insert and freed with the table: arrays of 4 *
- * max_kicks bytes, at most 2^17 of them and at most 1/8 of the table's
- * device memory, but at least 4096; keys that search a path beyond that many
+ * max_kicks bytes (in whole 16 bytes) in 1/8 of the table's device memory, at
+ * most 2^16 of them and at least 2^12, on tables too small for those as many as
+ * take 4/3 of the table's memory, but at least 2^10, and fewer (down to 2^10)
+ * where the device has no more memory; keys that search a path beyond that many
  * at once take turns.  (A first insert on a stream under capture takes it
- * from the device's stream-ordered memory pool.)  A dense batch, two keys per
+ * from the device's stream-ordered memory pool.)
+ * A dense batch, two keys per
  * bucket or more (one on 2^20 buckets and more), is binned by bucket first, in the path scratch or, if that
  * is too small, a second buffer of the table's own: 5/8 of the table's
- * device memory, at least 4 MiB, allocated on the first such batch and
+ * device memory, at least 1 MiB, allocated on the first such batch and
  * freed with the table (without it, on a stream under capture or out of
  * memory, the batch runs key by key, with the same results).  Two insert batches of one table must therefore not
  * overlap in time (order them on one stream).

@@ -203,15 +203,7 @@ int ckpp_create(ckpp_table **out, uint32_t log2_buckets, uint64_t hash_seed, uin
   if (lanes < 256) lanes = 256;
   if (lanes > kMaxPathLanes) lanes = kMaxPathLanes;
   t->path_lanes = (uint32_t)lanes;
-  // the table's own path arrays: one per lane of a launch while they stay
-  // within a small share of the table's memory, at least kOwnPathsMin
-  {
-    const uint64_t path_bytes = 4ull * ckpp::path_words(max_kicks);
-    uint64_t own = table_bytes(t) / ckpp::kOwnPathShare / path_bytes;
-    if (own > lanes) own = lanes;
-    if (own < ckpp::kOwnPathsMin) own = ckpp::kOwnPathsMin;
-    t->own_paths = (uint32_t)own;
-  }
+  t->own_paths = ckpp::own_paths(table_bytes(t), max_kicks);
 
   int rc = CKPP_OK;
   if (hipMalloc(&t->d_table, table_bytes(t)) != hipSuccess ||

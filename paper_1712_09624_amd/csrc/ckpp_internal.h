@@ -38,11 +38,26 @@ inline __host__ __device__ uint32_t path_words(uint32_t max_kicks) {
 // shared by the lanes of a wavefront) from a buffer of the table's own, kept
 // for its lifetime: the stream-ordered pool's allocate/free pair costs tens
 // of microseconds of host time per batch, during which the device idles, and
-// hundreds where the pool has given its memory back.  The buffer holds at
-// least kOwnPathsMin arrays, and more up to one per lane of the largest
-// launch while it stays within 1/kOwnPathShare of the table's own memory.
+// hundreds where the pool has given its memory back.  The buffer takes
+// 1/kOwnPathShare of the table's own memory, at most kOwnPathsMax arrays and at
+// least 4/3 of that memory (the bins of a dense batch that fills the table fit)
+// between kOwnPathsLow and kOwnPathsMin arrays, 2 and 8 MB at 500 kicks, so that
+// many small tables hold little.  Where the device has less memory left, the
+// buffer is halved down to kOwnPathsLow.  Fewer arrays slow down batches that
+// overfill a table, whose keys walk: 436,000 keys beyond load 0.95 of 2^20
+// buckets 350 ms with 1/8, 610 with 1/32; 1.7M of 2^22 570 and 1020.
+constexpr uint32_t kOwnPathsLow = 1024;
 constexpr uint32_t kOwnPathsMin = 4096;
+constexpr uint32_t kOwnPathsMax = 65536;
 constexpr uint64_t kOwnPathShare = 8;
+inline uint32_t own_paths(uint64_t table_bytes, uint32_t max_kicks) {
+  const uint64_t fill = table_bytes / (4ull * path_words(max_kicks)), least = fill * 4u / 3u;
+  const uint64_t low = least < kOwnPathsLow   ? kOwnPathsLow
+                       : least < kOwnPathsMin ? least
+                                              : kOwnPathsMin;
+  const uint64_t share = fill / kOwnPathShare;
+  return (uint32_t)(share < low ? low : share < kOwnPathsMax ? share : kOwnPathsMax);
+}
 
 // Dense insert batches (ckpp_bulk.hip).  Status of a key that waits for the
 // second stage.
@@ -67,7 +82,7 @@ inline uint64_t min_bulk_keys(uint32_t log2b) {
 // in two chunks with their slack, and no less than this.  A batch in more chunks
 // reads and writes the buckets' heads once per chunk (2^24 buckets at load
 // 0.9 with 0.5, 1.25 and 2.5 GiB: 21.7, 18.2 and 15.5 ms).
-constexpr uint64_t kMinBulkBytes = 4ull << 20;
+constexpr uint64_t kMinBulkBytes = 1ull << 20;
 
 // One work item of a plan: lookups [start, start + count) of the
 // concatenated key batch, all of one table, with that table's parameters

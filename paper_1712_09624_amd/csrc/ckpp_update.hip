@@ -313,7 +313,6 @@ hipError_t launch_insert(const ckpp_table *t, const void *d_keys, const uint64_t
                          const uint16_t *d_expiry, const TimerArgs *timers, uint64_t n,
                          uint8_t *d_status, uint64_t *d_nfailed, hipStream_t s) {
   ckpp_table *tm = const_cast<ckpp_table *>(t);
-  const uint64_t bytes = (uint64_t)t->own_paths * path_words(t->max_kicks) * sizeof(uint32_t);
   uint32_t *paths = t->d_own_paths;
   hipError_t e = hipSuccess;
   bool pooled = false;
@@ -324,8 +323,14 @@ hipError_t launch_insert(const ckpp_table *t, const void *d_keys, const uint64_t
     e = hipStreamIsCapturing(s, &capture);
     if (e != hipSuccess) return e;
     pooled = capture != hipStreamCaptureStatusNone;
-    e = pooled ? hipMallocAsync(reinterpret_cast<void **>(&paths), bytes, s)
-               : hipMalloc(reinterpret_cast<void **>(&paths), bytes);
+    for (;;) {
+      const uint64_t bytes = (uint64_t)t->own_paths * path_words(t->max_kicks) * sizeof(uint32_t);
+      e = pooled ? hipMallocAsync(reinterpret_cast<void **>(&paths), bytes, s)
+                 : hipMalloc(reinterpret_cast<void **>(&paths), bytes);
+      if (e != hipErrorOutOfMemory || pooled || t->own_paths < 2u * kOwnPathsLow) break;
+      (void)hipGetLastError();
+      tm->own_paths /= 2u;
+    }
     if (e != hipSuccess) return e;
     if (!pooled) tm->d_own_paths = paths;
   }

@@ -1,0 +1,61 @@
+"""Device memory that tables hold after inserts: small tables little."""
+
+import pytest
+
+from gpu_util import say
+from paper_1712_09624_amd import workload as W
+
+pytestmark = pytest.mark.gpu
+
+MIB = 1 << 20
+
+
+def free_bytes():
+    import torch
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    return torch.cuda.mem_get_info()[0]
+
+
+def draw(n, seed):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    keys = torch.randint(-(1 << 63), (1 << 63) - 1, (n, 2), dtype=torch.int64, device="cuda",
+                         generator=g).view(torch.uint8)
+    return keys, torch.arange(n, dtype=torch.int64, device="cuda") * 3 + 1
+
+
+def fill(t, keys, vals):
+    import torch
+    st = torch.empty(len(keys), dtype=torch.uint8, device="cuda")
+    nf = torch.zeros(1, dtype=torch.int64, device="cuda")
+    t.insert(keys, vals, status=st, nfailed=nf)
+    assert int(nf.item()) == 0 and not bool(st.any())
+
+
+def check(t, keys, vals):
+    import torch
+    f, v = t.lookup(keys)
+    assert bool(f.all()) and torch.equal(v, vals)
+    s = t.stats()
+    assert s["live"] == len(keys) and s["locked"] == 0 and s["retry_exhausted"] == 0
+
+
+# 1000 and 2000 keys one by one, 5000 as a dense batch
+@pytest.mark.parametrize("n", [1000, 2000, 5000])
+def test_small_tables_hold_little(n):
+    from paper_1712_09624_amd.ckpp import Table
+    keys, vals = draw(n, 3)
+    warm = Table(10, W.HASH_SEED, W.MAX_KICKS, device=0)
+    fill(warm, keys, vals)
+    tables = [Table(10, W.HASH_SEED, W.MAX_KICKS, device=0) for _ in range(32)]
+    before = free_bytes()
+    say(f"32 tables of 2^10 buckets, {n} keys each")
+    for t in tables:
+        fill(t, keys, vals)
+    held = (before - free_bytes()) / len(tables)
+    for t in tables:
+        check(t, keys, vals)
+        t.close()
+    warm.close()
+    assert held <= 3 * MIB, f"{held / MIB:.1f} MiB held per table"

@@ -1,0 +1,93 @@
+"""What device memory inserts take and keep, without a GPU: the library runs on
+a stand-in for the HIP runtime (fake_hip.c) that reports every allocation and
+can refuse large ones."""
+
+import os
+import subprocess
+import sys
+
+import pytest
+
+from paper_1712_09624_amd import ckpp
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+KICKS = 500
+MB = 10**6
+
+PROGRAM = """
+import ctypes, os, sys
+ctypes.CDLL(sys.argv[1], mode=os.RTLD_GLOBAL | os.RTLD_NOW)  # before the real runtime
+from paper_1712_09624_amd import ckpp
+lib = ckpp.load()
+libc = ctypes.CDLL(None)
+at = 1 << 20                      # an address nobody reads
+
+def largest(n):
+    libc.setenv(b"FAKE_HIP_LARGEST", str(n).encode(), 1)
+
+def table(B, kicks):
+    h = ctypes.c_void_p()
+    assert lib.ckpp_create(ctypes.byref(h), B, 1, kicks, 0, 0) == ckpp.OK
+    return h
+
+def insert(h, n, status=at):
+    print("insert", flush=True)
+    print("rc", lib.ckpp_insert_batch(h, at, at, n, status, None, None), flush=True)
+"""
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    fake = str(tmp_path_factory.mktemp("hip") / "fake_hip.so")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", fake,
+                    os.path.join(HERE, "fake_hip.c")], check=True)
+
+    def go(body):
+        """[(allocations of the insert as (call, bytes, granted), its status)]"""
+        out = subprocess.run([sys.executable, "-c", PROGRAM + body, fake], text=True, check=True,
+                             capture_output=True, cwd=os.path.dirname(HERE)).stdout
+        inserts = []
+        for part in out.split("insert\n")[1:]:
+            lines = [x.split() for x in part.splitlines()]
+            end = next(i for i, x in enumerate(lines) if x[0] == "rc")
+            inserts.append(([(c, int(n), ok == "ok") for c, n, ok in lines[:end]],
+                            int(lines[end][1])))
+        return inserts
+    return go
+
+
+@pytest.mark.parametrize("kicks", [0, 1, 100, KICKS, 4096])
+@pytest.mark.parametrize("B", [1, 10, 13, 15, 17, 20, 24])
+def test_path_scratch_follows_the_table(run, B, kicks):
+    """An insert key by key keeps path arrays of an eighth of the table, at
+    most 65536, and on small tables at least 1024 and at most 4096."""
+    (allocs, rc), = run(f"insert(table({B}, {kicks}), 1000, None)")
+    assert rc == ckpp.OK and len(allocs) == 1
+    call, held, ok = allocs[0]
+    path = 4 * max(4, (kicks + 3) // 4 * 4)
+    share = (256 << B) // 8
+    assert call == "malloc" and ok and held % path == 0
+    assert held // path >= 1024
+    assert held <= max(min(share, 65536 * path), 1024 * path,
+                       min(4096 * path, (256 << B) * 4 // 3))
+
+
+def test_path_scratch_with_little_memory_left(run):
+    """The buffer is halved where the device does not grant it; below the least
+    it is an error, and the table works once there is memory again."""
+    tight, none, again = run(f"""
+t = table(20, {KICKS})
+largest({10 * MB})
+insert(t, 5000)
+u = table(10, {KICKS})
+largest({MB})
+insert(u, 5000, None)
+largest({10 * MB})
+insert(u, 5000, None)
+""")
+    assert tight[1] == ckpp.OK
+    sizes = [n for _, n, _ in tight[0]]
+    assert sizes == sorted(sizes, reverse=True) and len(sizes) > 1
+    assert [ok for _, _, ok in tight[0]] == [False] * (len(sizes) - 1) + [True]
+    assert none[1] == ckpp.ENOMEM
+    assert again[1] == ckpp.OK and again[0][0][2]
