@@ -152,13 +152,19 @@ int ckpp_clear(ckpp_table *t, void *stream);
  * where the device has no more memory; keys that search a path beyond that many
  * at once take turns.  (A first insert on a stream under capture takes it
  * from the device's stream-ordered memory pool.)
- * A dense batch, two keys per
- * bucket or more (one on 2^20 buckets and more), is binned by bucket first, in the path scratch or, if that
- * is too small, a second buffer of the table's own: 5/8 of the table's
- * device memory, at least 1 MiB, allocated on the first such batch and
- * freed with the table (without it, on a stream under capture or out of
- * memory, the batch runs key by key, with the same results).  Two insert batches of one table must therefore not
- * overlap in time (order them on one stream).
+ * A dense batch is binned by bucket first: one with a d_status, of at least
+ * 4096 keys, no more than the table has slots, and at least two keys per bucket
+ * (one on 2^20 buckets and more), into a table with filters of at most 2^24
+ * buckets.  Its bins are in the path scratch or, if that is too small, in a
+ * second buffer of the table's own: 5/8 of the table's device memory, at least
+ * 1 MiB, allocated on the first such batch and freed with the table, while
+ * those of all tables of the device take at most 1/64 of its memory.  Beyond
+ * that a batch of 2^23 keys, two per bucket or more, takes its bins from the
+ * stream-ordered pool and returns them on `stream`.  Without bins (a smaller
+ * batch then, a stream under capture whose table keeps none, or no memory)
+ * the batch runs key by key, with the same results.
+ * Two insert batches of one table must therefore not overlap in time (order
+ * them on one stream).
  * Errors: CKPP_EINVAL (null table/keys/values with n > 0, misaligned keys),
  * CKPP_ENOMEM (scratch allocation failed). */
 int ckpp_insert_batch(ckpp_table *t, const void *d_keys, const uint64_t *d_values, uint64_t n,
@@ -328,7 +334,7 @@ typedef struct {
     uint64_t hash_seed;
     uint64_t image_bucket_bytes; /* sizes of the export/import arrays */
     uint64_t image_kv_bytes;
-    uint64_t device_bytes;       /* device memory of the table */
+    uint64_t device_bytes;       /* device memory of the buckets (no working areas) */
     void *d_table;               /* device address of the table */
 } ckpp_info_t;
 

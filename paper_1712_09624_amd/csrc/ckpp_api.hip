@@ -204,6 +204,7 @@ int ckpp_create(ckpp_table **out, uint32_t log2_buckets, uint64_t hash_seed, uin
   if (lanes > kMaxPathLanes) lanes = kMaxPathLanes;
   t->path_lanes = (uint32_t)lanes;
   t->own_paths = ckpp::own_paths(table_bytes(t), max_kicks);
+  t->device_mem = prop.totalGlobalMem;
 
   int rc = CKPP_OK;
   if (hipMalloc(&t->d_table, table_bytes(t)) != hipSuccess ||
@@ -233,7 +234,7 @@ int ckpp_destroy(ckpp_table *t) {
   (void)hipFree(t->d_table);
   (void)hipFree(t->d_stats);
   if (t->d_own_paths) (void)hipFree(t->d_own_paths);
-  if (t->d_bulk) (void)hipFree(t->d_bulk);
+  ckpp::bulk_free(t);
   delete t;
   return CKPP_OK;
 }

@@ -27,6 +27,8 @@
 // and records), 1.2 ms for their blocks, 2.1 ms for the 4M keys of the second
 // stage.
 
+#include <atomic>
+
 #include "ckpp_device.h"
 #include "ckpp_internal.h"
 
@@ -228,7 +230,30 @@ uint64_t bin_cap(uint64_t mean) {
   return mean + 4u * root + 16u;
 }
 
+// Bytes of bins that the tables of each device keep.
+constexpr int kMaxDevices = 64;
+std::atomic<uint64_t> g_kept[kMaxDevices];
+
+// Counts `bytes` of bins for the table, if its device's share has room.
+bool keep_bins(ckpp_table *t, uint64_t bytes) {
+  if (t->device >= kMaxDevices) return false;
+  std::atomic<uint64_t> &kept = g_kept[t->device];
+  uint64_t held = kept.load();
+  do {
+    if (held + bytes > t->device_mem / kBulkShare) return false;
+  } while (!kept.compare_exchange_weak(held, held + bytes));
+  t->bulk_bytes = bytes;
+  return true;
+}
+
 }  // namespace
+
+void bulk_free(ckpp_table *t) {
+  if (t->d_bulk) (void)hipFree(t->d_bulk);
+  if (t->bulk_bytes) g_kept[t->device] -= t->bulk_bytes;
+  t->d_bulk = nullptr;
+  t->bulk_bytes = 0;
+}
 
 hipError_t bulk_insert_primary(ckpp_table *t, const void *d_keys, const uint64_t *d_values,
                                const uint16_t *d_expiry, const TimerArgs *timers, uint64_t n,
@@ -246,7 +271,7 @@ hipError_t bulk_insert_primary(ckpp_table *t, const void *d_keys, const uint64_t
   // after them, if it is as large (on tables of up to 2^15 buckets at 500
   // kicks; with a buffer of their own the first such batch of a table of
   // 2^13 took 78 us instead of 63, its destruction 48 instead of 32), else a
-  // buffer of their own, kept.
+  // buffer of their own, kept while there is room for it (keep_bins).
   uint64_t limit = (256ull << log2b) / 8u * 5u;
   if (limit < kMinBulkBytes) limit = kMinBulkBytes;
   const uint64_t path_bytes = (uint64_t)t->own_paths * path_words(t->max_kicks) * 4u;
@@ -258,44 +283,55 @@ hipError_t bulk_insert_primary(ckpp_table *t, const void *d_keys, const uint64_t
     chunk = (n + chunks - 1u) / chunks;
   }
   A.cap = (uint32_t)bin_cap((chunk + A.bins - 1u) / A.bins);
-  if (!shared && !t->d_bulk) {
-    // not under capture, and without it the batch runs the other way
+  void *bins = shared ? static_cast<void *>(t->d_own_paths) : t->d_bulk;
+  bool pooled = false;
+  if (!bins) {
+    // no memory is taken under capture, and without it the batch runs the
+    // other way
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &capture) != hipSuccess ||
         capture != hipStreamCaptureStatusNone) {
       (void)hipGetLastError();
       return hipSuccess;
     }
-    void *p = nullptr;
-    if (hipMalloc(&p, limit) != hipSuccess) {
+    hipError_t e = hipErrorOutOfMemory;
+    if (keep_bins(t, limit)) {
+      e = hipMalloc(&bins, limit);
+      if (e == hipSuccess) t->d_bulk = static_cast<uint8_t *>(bins);
+      else bulk_free(t);
+    } else if (n >= min_pooled_bulk_keys(log2b)) {
+      e = hipMallocAsync(&bins, 32ull * A.bins * A.cap, s);
+      pooled = true;
+    }
+    if (e != hipSuccess) {
       (void)hipGetLastError();
       return hipSuccess;
     }
-    t->d_bulk = static_cast<uint8_t *>(p);
   }
   *taken = true;
   A.fill = t->d_bulk_fill;
-  A.recs = reinterpret_cast<uint4 *>(shared ? reinterpret_cast<uint8_t *>(t->d_own_paths)
-                                            : t->d_bulk);
+  A.recs = static_cast<uint4 *>(bins);
   A.bk = t->d_table;
   A.log2b = log2b;
   A.seed = t->seed;
   A.now = timers ? timers->now : 0u;
-  for (uint64_t i = 0; i < n; i += chunk) {
+  hipError_t e = hipSuccess;
+  for (uint64_t i = 0; i < n && e == hipSuccess; i += chunk) {
     A.keys = reinterpret_cast<const uint4 *>(d_keys) + i;
     A.vals = d_values + i;
     A.expiry = d_expiry ? d_expiry + i : nullptr;
     A.status = d_status + i;
     A.n = (uint32_t)(n - i < chunk ? n - i : chunk);
-    const hipError_t e = timers ? launch_bulk<true>(A, s) : launch_bulk<false>(A, s);
-    if (e != hipSuccess) {
-      // bins may be left filled: the next batch starts with empty ones
-      (void)hipDeviceSynchronize();
-      (void)hipMemset(t->d_bulk_fill, 0, kMaxBulkBins * sizeof(uint32_t));
-      return e;
-    }
+    e = timers ? launch_bulk<true>(A, s) : launch_bulk<false>(A, s);
   }
-  return hipSuccess;
+  if (e != hipSuccess) {
+    // bins may be left filled: the next batch starts with empty ones
+    (void)hipDeviceSynchronize();
+    (void)hipMemset(t->d_bulk_fill, 0, kMaxBulkBins * sizeof(uint32_t));
+  }
+  if (!pooled) return e;
+  const hipError_t f = hipFreeAsync(bins, s);
+  return e != hipSuccess ? e : f;
 }
 
 }  // namespace ckpp

@@ -17,8 +17,9 @@ struct ckpp_table {
   uint32_t *d_own_paths;    // the table's own cuckoo-path scratch (own_paths
                             // arrays), allocated on the first insert
   uint32_t own_paths;
-  uint8_t *d_bulk;      // bins of dense insert batches, allocated on the first
-                        // that the path scratch is too small for
+  uint8_t *d_bulk;      // bins of dense insert batches, if the table keeps them
+  uint64_t bulk_bytes;  // their size, counted against device_mem
+  uint64_t device_mem;  // the device's memory in bytes
   uint32_t *d_bulk_fill;  // records of each bin, zero between batches
   uint64_t *d_stats;    // device accumulator of ckpp_stats_t
   uint32_t retry_limit; // attempts per key on contended locks (ckpp_set_retry_limit)
@@ -83,6 +84,19 @@ inline uint64_t min_bulk_keys(uint32_t log2b) {
 // reads and writes the buckets' heads once per chunk (2^24 buckets at load
 // 0.9 with 0.5, 1.25 and 2.5 GiB: 21.7, 18.2 and 15.5 ms).
 constexpr uint64_t kMinBulkBytes = 1ull << 20;
+// Tables keep their bins while those of all tables of a device stay within
+// 1/kBulkShare of its memory (4.5 GiB on MI355X).  A batch beyond that takes
+// its bins from the stream-ordered pool and gives them back on its stream,
+// which costs a caller that waits for every batch about 300 us for 160 MiB to
+// 640 MiB and 620 us for 2.5 GiB (the pool returns its memory when the device
+// is idle), so only batches that save more than that do: of 2^23 keys and two
+// keys per bucket (2^21 buckets, 4 per bucket: 824 us and 1430 key by key; 2^22,
+// 2: 920 and 1294; 2^23, 1: 1108 and 1231, 2: 1736 and 2472).
+constexpr uint64_t kBulkShare = 64;
+inline uint64_t min_pooled_bulk_keys(uint32_t log2b) {
+  const uint64_t n = 2ull << log2b;
+  return n < (1ull << 23) ? 1ull << 23 : n;
+}
 
 // One work item of a plan: lookups [start, start + count) of the
 // concatenated key batch, all of one table, with that table's parameters
@@ -158,6 +172,8 @@ hipError_t launch_insert(const ckpp_table *t, const void *d_keys, const uint64_t
 hipError_t bulk_insert_primary(ckpp_table *t, const void *d_keys, const uint64_t *d_values,
                                const uint16_t *d_expiry, const TimerArgs *timers, uint64_t n,
                                uint8_t *d_status, hipStream_t s, bool *taken);
+// Frees the table's bins (nothing runs on the table).
+void bulk_free(ckpp_table *t);
 hipError_t launch_delete(const ckpp_table *t, const void *d_keys, uint64_t n,
                          const TimerArgs *timers, uint8_t *d_found, hipStream_t s);
 // The insert without any allocation (ckpp_insert_batch_noalloc): returns a

@@ -1,4 +1,6 @@
-"""Device memory that tables hold after inserts: small tables little."""
+"""Device memory that tables hold after inserts: small tables little, and the
+bins of dense batches a bounded share of the device over all tables, beyond
+which a batch gives its bins back or does without."""
 
 import pytest
 
@@ -59,3 +61,40 @@ def test_small_tables_hold_little(n):
         t.close()
     warm.close()
     assert held <= 3 * MIB, f"{held / MIB:.1f} MiB held per table"
+
+
+def test_bins_of_all_tables_are_bounded():
+    """Dense batches of ten tables, whose bins would take 6.25 GiB; then one
+    too small to be worth bins from the pool."""
+    import torch
+    from paper_1712_09624_amd.ckpp import Table
+    nt, n = 10, (1 << 23) + 13
+    keys, vals = draw(n, 4)
+    share = torch.cuda.mem_get_info()[1] // 64
+    bins = (256 << 22) * 5 // 8
+    assert nt * bins > share + 512 * MIB
+    tables = [Table(22, W.HASH_SEED, W.MAX_KICKS, device=0) for _ in range(nt)]
+    empty = free_bytes()
+    for t in tables:
+        fill(t, keys[:1], vals[:1])  # takes the path scratch
+        t.clear()
+    before = free_bytes()
+    for i, t in enumerate(tables):
+        say(f"dense batch of table {i}")
+        fill(t, keys, vals)
+    held = before - free_bytes()
+    small = Table(20, W.HASH_SEED, W.MAX_KICKS, device=0)
+    m = 1 << 21
+    say("dense batch of a smaller table")
+    fill(small, keys[:m], vals[:m])
+    check(small, keys[:m], vals[:m])
+    for t in tables:
+        check(t, keys, vals)
+    assert held <= share + 64 * MIB, f"{held / MIB:.0f} MiB held"
+    again = tables[-1]
+    say("the last table's batch again")
+    st, _ = again.insert(keys, vals)
+    assert bool((st == 1).all())
+    for t in (*tables, small):
+        t.close()
+    assert free_bytes() >= empty + nt * (256 << 22) - 64 * MIB

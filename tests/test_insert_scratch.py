@@ -91,3 +91,28 @@ insert(u, 5000, None)
     assert [ok for _, _, ok in tight[0]] == [False] * (len(sizes) - 1) + [True]
     assert none[1] == ckpp.ENOMEM
     assert again[1] == ckpp.OK and again[0][0][2]
+
+
+def test_bins_of_dense_batches_are_bounded(run):
+    """Tables keep the bins of their dense batches up to 1/64 of the device's
+    288 GiB in all; beyond it a batch takes them from the pool, or does without
+    when it is small, and a destroyed table's share is free again."""
+    got = run(f"""
+ts = [table(22, {KICKS}) for _ in range(10)]
+for t in ts:
+    insert(t, 1 << 24)
+insert(ts[0], 1 << 24)
+s = table(20, {KICKS})
+insert(s, 1 << 21)
+lib.ckpp_destroy(ts[0])
+insert(s, 1 << 21)
+""")
+    assert all(rc == ckpp.OK for _, rc in got)
+    bins = (256 << 22) * 5 // 8
+    kept = [a[1:] for a, _ in got[:10]]  # after the path scratch
+    room = (288 << 30) // 64 // bins
+    assert [c for a in kept for c, n, _ in a if c == "malloc" and n == bins] == ["malloc"] * room
+    assert all([c for c, _, _ in a] == ["pool"] and a[0][1] <= bins for a in kept[room:])
+    assert got[10][0] == []                                   # its bins were kept
+    assert [c for c, _, _ in got[11][0]] == ["malloc"]        # path scratch alone
+    assert got[12][0] == [("malloc", (256 << 20) * 5 // 8, True)]
