@@ -20,8 +20,6 @@ constexpr uint32_t kMaxKicksLimit = 4096;
 constexpr uint32_t kMaxPathLanes = 131072;
 constexpr ckpp_launch_t kStartLaunch = {8, 2, 128, 0};
 constexpr uint32_t kAccWords = 128;   // device accumulator words
-// ... and the bin counters of dense inserts behind them
-constexpr size_t kAccBytes = kAccWords * sizeof(uint64_t) + ckpp::kMaxBulkBins * sizeof(uint32_t);
 constexpr uint32_t kAccStats = 7 + CKPP_MOVED_BINS;
 constexpr uint32_t kAccRetry = 127;   // retry-bound counter (never cleared)
 
@@ -206,12 +204,15 @@ int ckpp_create(ckpp_table **out, uint32_t log2_buckets, uint64_t hash_seed, uin
   t->own_paths = ckpp::own_paths(table_bytes(t), max_kicks);
   t->device_mem = prop.totalGlobalMem;
 
+  // the accumulator, and the bin counters of dense inserts behind it
+  const size_t acc_bytes =
+      kAccWords * sizeof(uint64_t) + ckpp::bulk_bins(log2_buckets) * sizeof(uint32_t);
   int rc = CKPP_OK;
   if (hipMalloc(&t->d_table, table_bytes(t)) != hipSuccess ||
-      hipMalloc(&t->d_stats, kAccBytes) != hipSuccess) {
+      hipMalloc(&t->d_stats, acc_bytes) != hipSuccess) {
     rc = CKPP_ENOMEM;
   } else if (hipMemset(t->d_table, 0, table_bytes(t)) != hipSuccess ||
-             hipMemset(t->d_stats, 0, kAccBytes) != hipSuccess ||
+             hipMemset(t->d_stats, 0, acc_bytes) != hipSuccess ||
              hipDeviceSynchronize() != hipSuccess) {
     rc = CKPP_EDEVICE;
   }

@@ -248,6 +248,12 @@ bool keep_bins(ckpp_table *t, uint64_t bytes) {
 
 }  // namespace
 
+uint32_t bulk_bins(uint32_t log2b) {
+  if (log2b < kMinBinShift + 1u || log2b > kMaxBulkLog2Buckets || (8ull << log2b) < kMinBulkKeys)
+    return 0u;
+  return 1u << (log2b - bin_shift(log2b));
+}
+
 void bulk_free(ckpp_table *t) {
   if (t->d_bulk) (void)hipFree(t->d_bulk);
   if (t->bulk_bytes) g_kept[t->device] -= t->bulk_bytes;
@@ -260,12 +266,12 @@ hipError_t bulk_insert_primary(ckpp_table *t, const void *d_keys, const uint64_t
                                uint8_t *d_status, hipStream_t s, bool *taken) {
   *taken = false;
   const uint32_t log2b = t->log2_buckets;
-  if ((t->flags & CKPP_PLAIN) || !d_status || log2b < kMinBinShift + 1u ||
-      log2b > kMaxBulkLog2Buckets || n < min_bulk_keys(log2b) || n > (8ull << log2b))
-    return hipSuccess;
   BulkArgs A;
+  A.bins = bulk_bins(log2b);
+  if ((t->flags & CKPP_PLAIN) || !d_status || A.bins == 0u || n < min_bulk_keys(log2b) ||
+      n > (8ull << log2b))
+    return hipSuccess;
   A.shift = bin_shift(log2b);
-  A.bins = 1u << (log2b - A.shift);
   // The bins take a share of the table's memory, in which the batch runs in
   // equal chunks: the cuckoo-path scratch, which the second stage needs only
   // after them, if it is as large (on tables of up to 2^15 buckets at 500
@@ -327,7 +333,7 @@ hipError_t bulk_insert_primary(ckpp_table *t, const void *d_keys, const uint64_t
   if (e != hipSuccess) {
     // bins may be left filled: the next batch starts with empty ones
     (void)hipDeviceSynchronize();
-    (void)hipMemset(t->d_bulk_fill, 0, kMaxBulkBins * sizeof(uint32_t));
+    (void)hipMemset(t->d_bulk_fill, 0, A.bins * sizeof(uint32_t));
   }
   if (!pooled) return e;
   const hipError_t f = hipFreeAsync(bins, s);

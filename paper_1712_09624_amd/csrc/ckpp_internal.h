@@ -172,6 +172,8 @@ hipError_t launch_insert(const ckpp_table *t, const void *d_keys, const uint64_t
 hipError_t bulk_insert_primary(ckpp_table *t, const void *d_keys, const uint64_t *d_values,
                                const uint16_t *d_expiry, const TimerArgs *timers, uint64_t n,
                                uint8_t *d_status, hipStream_t s, bool *taken);
+// Bins of the dense batches of a table of 2^log2b buckets (0: it takes none).
+uint32_t bulk_bins(uint32_t log2b);
 // Frees the table's bins (nothing runs on the table).
 void bulk_free(ckpp_table *t);
 hipError_t launch_delete(const ckpp_table *t, const void *d_keys, uint64_t n,

@@ -42,14 +42,17 @@ def run(tmp_path_factory):
     subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", fake,
                     os.path.join(HERE, "fake_hip.c")], check=True)
 
-    def go(body):
-        """[(allocations of the insert as (call, bytes, granted), its status)]"""
+    def go(body, created=None):
+        """[(allocations of the insert as (call, bytes, granted), its status)];
+        the bytes of those after the first insert's end go to `created`."""
         out = subprocess.run([sys.executable, "-c", PROGRAM + body, fake], text=True, check=True,
                              capture_output=True, cwd=os.path.dirname(HERE)).stdout
         inserts = []
         for part in out.split("insert\n")[1:]:
             lines = [x.split() for x in part.splitlines()]
             end = next(i for i, x in enumerate(lines) if x[0] == "rc")
+            if created is not None and not inserts:
+                created += [int(n) for _, n, _ in lines[end + 1:]]
             inserts.append(([(c, int(n), ok == "ok") for c, n, ok in lines[:end]],
                             int(lines[end][1])))
         return inserts
@@ -70,6 +73,21 @@ def test_path_scratch_follows_the_table(run, B, kicks):
     assert held // path >= 1024
     assert held <= max(min(share, 65536 * path), 1024 * path,
                        min(4096 * path, (256 << B) * 4 // 3))
+
+
+@pytest.mark.parametrize("B,bins", [(1, 0), (8, 0), (9, 16), (15, 512), (22, 1 << 14),
+                                    (24, 1 << 14), (25, 0)])
+def test_bin_counters_follow_the_table(run, B, bins):
+    """Beside its buckets a table takes 1 KiB and a word per bin of its dense
+    batches (seen by creating it between two inserts)."""
+    (_, first), (_, second) = run(f"""
+t = table(10, {KICKS})
+insert(t, 1000)
+u = table({B}, {KICKS})
+insert(t, 1000)
+""", created := [])
+    assert first == second == ckpp.OK
+    assert created == [256 << B, 1024 + 4 * bins]
 
 
 def test_path_scratch_with_little_memory_left(run):
