@@ -24,7 +24,7 @@ struct ckpp_table {
   uint64_t *d_stats;    // device accumulator of ckpp_stats_t
   uint32_t retry_limit; // attempts per key on contended locks (ckpp_set_retry_limit)
   ckpp_launch_t lookup_launch;
-  bool launch_set;      // a caller set lookup_launch (else small batches take their own shape)
+  bool launch_set;      // a caller set lookup_launch (else batches take their own shape)
   int num_cus;
 };
 
@@ -65,12 +65,20 @@ inline uint32_t own_paths(uint64_t table_bytes, uint32_t max_kicks) {
 constexpr uint8_t kInsertPending = 0xffu;
 // The batches that take that way hold at least kMinBulkKeys keys and, per
 // bucket of the table, one on 2^20 buckets and more, two on fewer.  Measured
-// on MI355X, this way and the other, from empty and from load 0.5, in us:
-// one key per bucket, 2^18 buckets 36 and 39, 61 and 57; 2^20 buckets 132 and
-// 205, 194 and 232; 2^22 buckets 548 and 664, 698 and 791; 2^24 buckets 2093
-// and 2562, 2580 and 2945; half a key, 2^22 buckets 383 and 338, 431 and 391.
-// One and a half, 2^16 buckets 21 and 27, 54 and 45.  Larger tables have more
-// bins than fit the counters in LDS.
+// on MI355X, this way and key by key, in us, at the line and beside it.  From
+// 2^20 buckets on it is faster from every load: one key per bucket, 2^20
+// buckets 131 and 185 from empty, 165 and 223 from load 0.5, 305 and 347 from
+// 0.8; 2^22 585 and 652, 715 and 776, 1175 and 1223; 2^24 2164 and 2521, 2621
+// and 2909, 4273 and 4411; one and a half from 0.8 (to 0.99) 1419 and 1524,
+// 3766 and 3900, 12154 and 12993; half a key, 2^22 383 and 338 from empty.
+// Below, two keys per bucket: 2^12 17.8 and 22.4 from empty, 34 and 40 from
+// 0.5, 76 and 83 from 0.7; 2^14 21.5 and 24.4, 41 and 46, 85 and 111; 2^16 29
+// and 34, 55 and 54, 130 and 121; 2^18 70 and 69, 95 and 104, 206 and 204: 6%
+// faster on average over 2^11..2^19 buckets and those loads, single points from
+// 24% faster to 9% slower.  Fewer keys lose there from load 0.5 on: one and a
+// half, 2^16 21 and 27 from empty, 54 and 45; one, 2^18 36 and 39, 61 and 57.
+// Tables of more than 2^24 buckets would need bins of more than 2^10 buckets,
+// which was not measured.
 constexpr uint64_t kMinBulkKeys = 4096;
 constexpr uint32_t kMaxBulkLog2Buckets = 24;
 constexpr uint32_t kMaxBulkLog2Bins = 14;  // their counters in LDS: 64 KiB

@@ -254,8 +254,9 @@ __global__ void __launch_bounds__(kScanBlock)
 
 namespace {
 
-// Launches an insert of A.n keys with `npaths` path arrays at A.paths
-// (npaths >= kMinPaths): one key per wavefront for few keys, else one lane
+// Launches an insert of A.n keys with `npaths` path arrays at A.paths (at
+// least the four that the wavefronts of one block need; the callers have 512
+// and more): one key per wavefront for few keys, else one lane
 // per key on at most t->path_lanes lanes and npaths wavefronts.
 // marked: only the keys whose status is kInsertPending.
 hipError_t launch_insert_kernel(const ckpp_table *t, InsertArgs A, bool timed, bool marked,
