@@ -302,7 +302,7 @@ hipError_t bulk_insert_primary(ckpp_table *t, const void *d_keys, const uint64_t
     }
     hipError_t e = hipErrorOutOfMemory;
     if (keep_bins(t, limit)) {
-      e = hipMalloc(&bins, limit);
+      e = malloc_beside_capture(&bins, limit);
       if (e == hipSuccess) t->d_bulk = static_cast<uint8_t *>(bins);
       else bulk_free(t);
     } else if (n >= min_pooled_bulk_keys(log2b)) {

@@ -60,6 +60,18 @@ inline uint32_t own_paths(uint64_t table_bytes, uint32_t max_kicks) {
   return (uint32_t)(share < low ? low : share < kOwnPathsMax ? share : kOwnPathsMax);
 }
 
+// hipMalloc for a buffer that an insert finds it needs, which may be while
+// another stream is captured: outside the relaxed mode it would fail and break
+// that capture.  (The memory belongs to no graph.)
+inline hipError_t malloc_beside_capture(void **p, size_t bytes) {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  hipError_t e = hipThreadExchangeStreamCaptureMode(&mode);
+  if (e != hipSuccess) return e;
+  e = hipMalloc(p, bytes);
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  return e;
+}
+
 // Dense insert batches (ckpp_bulk.hip).  Status of a key that waits for the
 // second stage.
 constexpr uint8_t kInsertPending = 0xffu;

@@ -327,7 +327,7 @@ hipError_t launch_insert(const ckpp_table *t, const void *d_keys, const uint64_t
     for (;;) {
       const uint64_t bytes = (uint64_t)t->own_paths * path_words(t->max_kicks) * sizeof(uint32_t);
       e = pooled ? hipMallocAsync(reinterpret_cast<void **>(&paths), bytes, s)
-                 : hipMalloc(reinterpret_cast<void **>(&paths), bytes);
+                 : malloc_beside_capture(reinterpret_cast<void **>(&paths), bytes);
       if (e != hipErrorOutOfMemory || pooled || t->own_paths < 2u * kOwnPathsLow) break;
       (void)hipGetLastError();
       tm->own_paths /= 2u;

@@ -30,6 +30,7 @@ int hipMallocAsync(void **p, size_t n, void *s) { return (void)s, take("pool", p
 int hipFree(void *p) { return free(p), kOk; }
 int hipFreeAsync(void *p, void *s) { return (void)s, free(p), kOk; }
 int hipMemset(void *p, int v, size_t n) { return (void)p, (void)v, (void)n, kOk; }
+int hipThreadExchangeStreamCaptureMode(int *mode) { return (void)mode, kOk; }
 int hipStreamIsCapturing(void *s, int *status) { return (void)s, *status = 0, kOk; }
 int hipGetDevicePropertiesR0600(void *prop, int d) {
   /* name, uuid, luid, luidDeviceNodeMask, totalGlobalMem: 288 GiB at byte 288 */

@@ -98,3 +98,54 @@ def test_bins_of_all_tables_are_bounded():
     for t in (*tables, small):
         t.close()
     assert free_bytes() >= empty + nt * (256 << 22) - 64 * MIB
+
+
+# 5000 keys one by one and a dense batch, whose bins need a buffer of their own
+@pytest.mark.parametrize("thread", [False, True], ids=["same_thread", "other_thread"])
+@pytest.mark.parametrize("n", [5000, 2 << 16])
+def test_first_insert_beside_a_capture(n, thread):
+    """A table's first insert, on a stream of its own, while another stream is
+    captured: both the insert and the capture work."""
+    import threading
+    import torch
+    from paper_1712_09624_amd.ckpp import Table
+    keys, vals = draw(n, 5)
+    old = Table(10, W.HASH_SEED, W.MAX_KICKS, device=0)
+    fill(old, keys[:500], vals[:500])
+    t = Table(16, W.HASH_SEED, W.MAX_KICKS, device=0)
+    st = torch.empty(n, dtype=torch.uint8, device="cuda")
+    nf = torch.zeros(1, dtype=torch.int64, device="cuda")
+    found = torch.empty(500, dtype=torch.uint8, device="cuda")
+    got = torch.empty(500, dtype=torch.int64, device="cuda")
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    say(f"first insert of {n} keys beside a capture")
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        old.lookup(keys[:500], found=found, values=got)
+        if thread:
+            failed = []
+
+            def insert():
+                try:
+                    t.insert(keys, vals, status=st, nfailed=nf, stream=side)
+                except Exception as e:  # noqa: BLE001 -- reported by the test
+                    failed.append(e)
+
+            worker = threading.Thread(target=insert)
+            worker.start()
+            worker.join()
+            assert not failed
+        else:
+            t.insert(keys, vals, status=st, nfailed=nf, stream=side)
+    torch.cuda.synchronize()
+    assert int(nf.item()) == 0 and not bool(st.any())
+    check(t, keys, vals)
+    for rep in range(3):
+        found.zero_()
+        say(f"replay {rep}")
+        g.replay()
+        torch.cuda.synchronize()
+        assert bool(found.all()) and torch.equal(got, vals[:500])
+    t.close()
+    old.close()
